@@ -126,16 +126,12 @@ const char* mochy_last_error(const mochy_ctx* ctx);
                                   if the key would need too many node sets) or always
                                   those 16 (1); same hits */
 #define MOCHY_OPT_BATCH_LAUNCH 7  /* exact counting of a batch (mochy_profile) launches the
-                                     group-pair kernel once for the whole batch (1), once
-                                     per graph (2; batches of at most 256 graphs, larger
-                                     ones take one launch), or per graph when the graphs
-                                     average a full grid of work items each (0, default);
-                                     same counts */
-#define MOCHY_OPT_PAIR_BLOCKS 8  /* waves of the exact pair kernel launched per compute
-                                    unit, in fours, 1..16 (default 8: 32 waves, as blocks
-                                    of 256 threads, or half as many blocks of 512 where
-                                    one histogram serves a whole graph; a launch per graph
-                                    takes at most one wave per work item); same counts */
+                                     pair kernels once for the whole batch (1, and 0, the
+                                     default) or once per graph (2); same counts */
+#define MOCHY_OPT_PAIR_BLOCKS 8  /* waves launched per compute unit, in fours, 1..16 (default
+                                    8: 32 waves), by the pair kernel that takes a lane per
+                                    pair (rows of few neighbour groups, every-pair counting);
+                                    no launch has more waves than work items; same counts */
 #define MOCHY_OPT_CACHE_BYTES 9  /* device buffers of 64 MiB or more that a call frees are
                                     kept by the context, up to this many bytes in all, and
                                     reused by later calls on it (default half of the

@@ -19,13 +19,14 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libmochy.so")
 OBJDIR = os.path.join(HERE, "_build")
 
-SOURCES = ["patterns.cpp", "scan.hip", "project.hip", "exact.hip", "correct.hip", "sampled.hip",
+SOURCES = ["patterns.cpp", "scan.hip", "project.hip", "exact.hip", "pairs.hip", "correct.hip", "sampled.hip",
            "free.hip", "memo.hip", "calibrate.hip", "noalloc.hip", "api.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-mfma-vgpr-form",  # MFMA results in vector registers, read without copies
     "-I", INCLUDE, "-I", CSRC, "-Wall", "-Wno-unused-result",
 ]
 

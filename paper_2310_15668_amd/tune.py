@@ -1,11 +1,10 @@
 """Launch-shape autotuner for the batched exact pass (``mochy_profile``).
 
-Two launch choices of the group-pair kernel change its speed and never its
-counts:
+Two launch choices of the group-pair kernels change their speed and never
+their counts:
 
-* ``MOCHY_OPT_BATCH_LAUNCH``: one launch over the whole batch (1), whose
-  waves carry two histogram copies each and overlap the graphs' tails, or
-  one launch per graph (2), whose blocks share four copies;
+* ``MOCHY_OPT_BATCH_LAUNCH``: one launch over the whole batch (1, the
+  default), which overlaps the graphs' tails, or one launch per graph (2);
 * ``MOCHY_OPT_PAIR_BLOCKS``: blocks launched per compute unit.
 
 Which is faster depends on how the batch's work is spread over its graphs.
