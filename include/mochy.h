@@ -319,7 +319,8 @@ mochy_status mochy_phase_ms(const mochy_ctx* ctx, double* ms);
  * when open), out[5] rows regrouped with more hash parts than first
  * guessed, out[6] most hash parts of one row, out[7] hyperedge pairs sharing
  * a light node (the correction's pairs), out[8] row entries the correction
- * scanned, out[9] common neighbours it examined (centres of a light pair),
+ * scanned (centres that cannot need it are left out where the row's order
+ * tells), out[9] common neighbours it examined (centres of a light pair),
  * out[10] of those, the centres whose class it changed, out[11] the
  * sub-batches a mochy_profile call counted its graphs in (a batch that does
  * not fit in device memory is split).  Zeros for parts a call did not run

@@ -158,6 +158,42 @@ __global__ void k_scatter_pairs(int64_t n, const int2* __restrict__ flat, const 
   }
 }
 
+// First position of an ascending row whose id is v or more, by the whole wave:
+// 64 probes a step, so three dependent loads where a row has up to 2^18 ids.
+__device__ __forceinline__ int row_lower(const int32_t* __restrict__ row, int n, int64_t v, int lane) {
+  int lo = 0;
+  while (n > 0) {  // the answer is in [lo, lo + n]
+    const int step = (n + kWave - 1) / kWave;
+    const int at = lane * step;
+    const int below = __popcll(__ballot(at < n && row[lo + at] < v));  // probes are ascending
+    if (below == 0) break;
+    lo += (below - 1) * step + 1;
+    n = min(step - 1, n - ((below - 1) * step + 1));
+  }
+  return lo;
+}
+
+// The part [r_lo, r_hi) of row k that can need a fix: centres of [c0, c1) and,
+// where e_j and e_k share a heavy node, those below both.  A centre not below
+// both has its pair counted only if the two looked disjoint, and with a heavy
+// node v shared they never do (v is in the triple overlap, or outside e_i with
+// a bit of its own).  Rows are ascending, so both cut the row's ends; two
+// thirds of the entries of medium's partner rows belong to such pairs.
+// [e0, e1): the graph's hyperedges.
+__device__ __forceinline__ void fix_range(const int32_t* __restrict__ row, int d, const int32_t* __restrict__ up_first,
+                                          int32_t j, int32_t k, uint32_t Hk, int64_t c0, int64_t c1, int64_t e0,
+                                          int64_t e1, int lane, int& r_lo, int& r_hi) {
+  r_lo = c0 > e0 ? row_lower(row, d, c0, lane) : 0;
+  r_hi = d;
+  if (Hk != 0u) {
+    const int32_t m = min(j, k);
+    if (m >= c1) r_hi = row_lower(row, d, c1, lane);
+    else r_hi = m == k ? up_first[k] : row_lower(row, d, m, lane);
+  } else if (c1 < e1) {
+    r_hi = row_lower(row, d, c1, lane);
+  }
+}
+
 // Workgroups are dealt to the 8 XCDs in turn; block b takes the owner that
 // gives each XCD a contiguous range of the owner list (a bijection onto
 // [0, nb)), so that owners listed together share one XCD's L2.
@@ -188,9 +224,9 @@ __global__ __launch_bounds__(kFixThreads) __attribute__((amdgpu_waves_per_eu(8))
     const int32_t* __restrict__ partners,
     const int64_t* __restrict__ edge_ptr, const int32_t* __restrict__ edge_nodes,
     const int8_t* __restrict__ heavy_bit, const int64_t* __restrict__ lg_ptr,
-    const int32_t* __restrict__ lg_col, const uint32_t* __restrict__ recm,
+    const int32_t* __restrict__ lg_col, const int32_t* __restrict__ up_first, const uint32_t* __restrict__ recm,
     const uint16_t* __restrict__ rsz, const uint16_t* __restrict__ code_to_id3,
-    unsigned long long* hist_out, uint2* tally) {
+    unsigned long long* hist_out, unsigned long long* tally) {
   extern __shared__ uint32_t sm[];
   __shared__ uint16_t lut[kNumCodes];
   // kFixCopies histogram copies, lane l adding to copy l % kFixCopies (fewer
@@ -199,7 +235,7 @@ __global__ __launch_bounds__(kFixThreads) __attribute__((amdgpu_waves_per_eu(8))
   __shared__ unsigned long long hist[kFixCopies * kHistSlots];
   __shared__ int32_t part[kFixThreads];
   __shared__ int32_t ej[MOCHY_MAX_EDGE];  // e_j's nodes (ascending)
-  __shared__ uint32_t s_tally[2];  // centres examined, centres reclassified
+  __shared__ unsigned long long s_tally[3];  // entries scanned, centres examined, centres reclassified
   const int64_t it = xcd_block(blockIdx.x, gridDim.x);
   const int64_t ob = item_owner[it];
   const int32_t j = owners[ob];
@@ -207,7 +243,8 @@ __global__ __launch_bounds__(kFixThreads) __attribute__((amdgpu_waves_per_eu(8))
   const int64_t p1 = min(poff[ob + 1], p0 + kFixChunk);
   const int gj = row_graph[j];
   const int64_t e0 = geoff[gj];  // row j's graph owns hyperedges [e0, geoff[gj + 1])
-  const int nwE = int((geoff[gj + 1] - e0 + 31) / 32);
+  const int64_t e1 = geoff[gj + 1];
+  const int nwE = int((e1 - e0 + 31) / 32);
   uint32_t* bm = sm;          // row j over the graph's hyperedge ids
   uint32_t* rank = sm + nwE;  // set bits before each word
   const int64_t jb = lg_ptr[j];
@@ -217,10 +254,7 @@ __global__ __launch_bounds__(kFixThreads) __attribute__((amdgpu_waves_per_eu(8))
   for (int w = threadIdx.x; w < nwE; w += blockDim.x) bm[w] = 0;
   const uint32_t sizej = uint32_t(edge_ptr[j + 1] - edge_ptr[j]);
   if (threadIdx.x < sizej) ej[threadIdx.x] = edge_nodes[edge_ptr[j] + threadIdx.x];
-  if (threadIdx.x == 0) {
-    s_tally[0] = 0u;
-    s_tally[1] = 0u;
-  }
+  if (threadIdx.x < 3) s_tally[threadIdx.x] = 0ull;
   __syncthreads();
   for (int p = threadIdx.x; p < dj; p += blockDim.x) {
     const int64_t x = lg_col[jb + p] - e0;
@@ -251,7 +285,7 @@ __global__ __launch_bounds__(kFixThreads) __attribute__((amdgpu_waves_per_eu(8))
   // no lanes idle)
   const int lane = int(threadIdx.x) & (kWave - 1), wave = int(threadIdx.x) / kWave;
   unsigned long long* myhist = hist + (lane & (kFixCopies - 1)) * kHistSlots;
-  uint32_t n_centres = 0, n_changed = 0;  // this wave's, for mochy_exact_stats
+  uint32_t n_scanned = 0, n_centres = 0, n_changed = 0;  // this wave's, for mochy_exact_stats
   for (int64_t pp = p0 + wave; pp < p1; pp += kFixThreads / kWave) {
     const int32_t k = partners[pp];
     // masks over e_k's nodes: e_j ∩ e_k (mkj), its heavy and light nodes
@@ -266,7 +300,9 @@ __global__ __launch_bounds__(kFixThreads) __attribute__((amdgpu_waves_per_eu(8))
     const uint32_t mkj = uint32_t(__ballot(in_j));
     const uint32_t Hk = mkj & uint32_t(__ballot(heavy)), Lk = mkj & ~Hk;
     const int64_t kb = lg_ptr[k];
-    const int dk = int(lg_ptr[k + 1] - kb);
+    int r_lo, dk;
+    fix_range(lg_col + kb, int(lg_ptr[k + 1] - kb), up_first, j, k, Hk, c0, c1, e0, e1, lane, r_lo, dk);
+    n_scanned += uint32_t(max(dk - r_lo, 0));
     // row k scanned kUnroll entries per thread at a time; the loads of one
     // stage are issued together, with no branch between them (an entry that
     // is not a centre reads a valid dummy slot), since the work is bound by
@@ -274,7 +310,7 @@ __global__ __launch_bounds__(kFixThreads) __attribute__((amdgpu_waves_per_eu(8))
     // (7 entries per lane fit the 64 registers; 8 spill and were slower)
     constexpr int kUnroll = 7;
     constexpr int step = kWave;
-    for (int r0 = lane; r0 < dk; r0 += kUnroll * step) {
+    for (int r0 = r_lo + lane; r0 < dk; r0 += kUnroll * step) {
       int32_t iv[kUnroll];
       uint32_t mki[kUnroll];
 #pragma unroll
@@ -288,7 +324,7 @@ __global__ __launch_bounds__(kFixThreads) __attribute__((amdgpu_waves_per_eu(8))
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         const int32_t i = iv[u];
-        const bool in = i >= c0 && i < c1;  // also excludes the -1 past the row's end
+        const bool in = i >= 0;  // not past the scanned part's end
         const int64_t il = in ? i - e0 : 0;
         const uint32_t iw = bm[il >> 5];
         const uint32_t ibit = 1u << (il & 31);
@@ -321,12 +357,13 @@ __global__ __launch_bounds__(kFixThreads) __attribute__((amdgpu_waves_per_eu(8))
       }
     }
   }
-  if (lane == 0 && (n_centres | n_changed) != 0u) {
-    atomicAdd(&s_tally[0], n_centres);
-    atomicAdd(&s_tally[1], n_changed);
+  if (lane == 0 && n_scanned != 0u) {
+    atomicAdd(&s_tally[0], (unsigned long long)n_scanned);
+    atomicAdd(&s_tally[1], (unsigned long long)n_centres);
+    atomicAdd(&s_tally[2], (unsigned long long)n_changed);
   }
   __syncthreads();
-  if (threadIdx.x == 0) tally[it] = make_uint2(s_tally[0], s_tally[1]);  // summed by k_fix_tally
+  if (threadIdx.x < 3) tally[it * 3 + threadIdx.x] = s_tally[threadIdx.x];  // summed by k_fix_tally
   for (int t = threadIdx.x; t < kHistSlots; t += blockDim.x) {
     unsigned long long v = 0;
     for (int c = 0; c < kFixCopies; ++c) v += hist[c * kHistSlots + t];
@@ -334,25 +371,17 @@ __global__ __launch_bounds__(kFixThreads) __attribute__((amdgpu_waves_per_eu(8))
   }
 }
 
-// The correction's work counters for mochy_exact_stats: row entries scanned
-// (the partner row of every light pair) and the per-item tallies of the fix
-// kernel, summed over a fixed grid with one atomic per block and counter
-// (atomics on one address from every wave or item would serialize).
-constexpr int kTallyBlocks = 256;
-__global__ __launch_bounds__(256) void k_fix_tally(int64_t npairs, const int32_t* __restrict__ partners,
-                                                   const int64_t* __restrict__ lg_ptr, int64_t nitems,
-                                                   const uint2* __restrict__ tally, unsigned long long* stats) {
+// The correction's work counters for mochy_exact_stats: the per-item tallies
+// of the fix kernel, summed over a fixed grid with one atomic per block and
+// counter (atomics on one address from every wave or item would serialize).
+constexpr int kTallyBlocks = 64;
+__global__ __launch_bounds__(256) void k_fix_tally(int64_t nitems, const unsigned long long* __restrict__ tally,
+                                                   unsigned long long* stats) {
   __shared__ unsigned long long red[3][256 / kWave];
   unsigned long long v[3] = {0, 0, 0};
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  for (int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < npairs; p += stride) {
-    const int32_t k = partners[p];
-    v[0] += (unsigned long long)(lg_ptr[k + 1] - lg_ptr[k]);
-  }
-  for (int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; q < nitems; q += stride) {
-    v[1] += tally[q].x;
-    v[2] += tally[q].y;
-  }
+  for (int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; q < nitems; q += stride)
+    for (int x = 0; x < 3; ++x) v[x] += tally[q * 3 + x];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   for (int x = 0; x < 3; ++x) {
     for (int off = kWave / 2; off > 0; off >>= 1) v[x] += __shfl_xor(v[x], off, kWave);
@@ -416,7 +445,7 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
   int32_t* partners = nullptr;
   int64_t* ioff = nullptr;
   int32_t* item_owner = nullptr;
-  uint2* tally = nullptr;
+  unsigned long long* tally = nullptr;
   int64_t* noff = nullptr;
   int2* flat = nullptr;
   auto done = [&](mochy_status s) {
@@ -496,17 +525,17 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
   MOCHY_HIP_OR(hipStreamSynchronize(st), done);
   const int64_t nitems = ctx->h_small[506];
   if ((rc = device_alloc(ctx, (void**)&item_owner, size_t(nitems) * 4)) != MOCHY_OK ||
-      (rc = device_alloc(ctx, (void**)&tally, size_t(nitems) * 8)) != MOCHY_OK)
+      (rc = device_alloc(ctx, (void**)&tally, size_t(nitems) * 24)) != MOCHY_OK)
     return done(rc);
   k_item_owners<<<blocks(nowners, 256), 256, 0, st>>>(nowners, ioff, item_owner);
   phase_begin(ctx, kPhFix);
   k_light_fix<<<unsigned(nitems), kFixThreads, dyn, st>>>(c0, c1, g->row_graph, g->geoff, owners, item_owner,
                                                           ioff, poff, partners,
                                                            g->edge_ptr, g->edge_nodes, g->heavy_bit, g->lg_ptr,
-                                                           g->lg_col, g->recm, g->rsz, ctx->d_code_to_id3,
+                                                           g->lg_col, g->up_first, g->recm, g->rsz, ctx->d_code_to_id3,
                                                            (unsigned long long*)d_hist, tally);
   phase_end(ctx, kPhFix);
-  k_fix_tally<<<kTallyBlocks, 256, 0, st>>>(npairs, partners, g->lg_ptr, nitems, tally, stats);
+  k_fix_tally<<<kTallyBlocks, 256, 0, st>>>(nitems, tally, stats);
   MOCHY_HIP_OR(hipGetLastError(), done);
   MOCHY_HIP_OR(hipStreamSynchronize(st), done);
   return done(MOCHY_OK);
