@@ -333,6 +333,7 @@ extern "C" mochy_status mochy_ctx_create(int device, void* hip_stream, mochy_ctx
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) != hipSuccess) return fail(MOCHY_EDEVICE);
   ctx->num_cus = prop.multiProcessorCount;
+  ctx->total_mem = int64_t(prop.totalGlobalMem);
   ctx->cache_limit = int64_t(prop.totalGlobalMem / 2);
   ctx->group_cap_bytes = int64_t(prop.totalGlobalMem / 2);
   if (hip_stream) {

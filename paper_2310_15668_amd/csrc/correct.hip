@@ -20,7 +20,9 @@
 //        r5h = popcount(H & ~m_ki)                   heavy part of R5
 //        ls  = popcount(L & ~m_ki)                   light part of R5
 //     and |e_j ∩ e_i|, |e_i| from the size word of row j at e_i's position
-//     (the only read outside the scanned row).
+//     (the only read outside the scanned row).  Where memory allows, a byte
+//     table of the overlaps |e_j ∩ e_i| takes the place of the bitmap
+//     (k_light_dense, the usual path).
 //     If ls = 0 the pair kernel was exact at this centre.  Otherwise the pair
 //     kernel recorded the class with R5 = r5h, counted iff both neighbours
 //     are above e_i or the two looked disjoint; the exact class has
@@ -29,6 +31,7 @@
 //     added.
 #include "classify.h"
 #include "common.h"
+#include "pairs.h"
 
 namespace {
 
@@ -91,20 +94,56 @@ __global__ __launch_bounds__(256) void k_light_pairs(
   }
 }
 
-// The flat list of candidate slots (slot noff[w] + b (b - 1) / 2 + a for
-// members a < b of E_w): (owner, partner), or (-1, -1) where w is not the
-// pair's smallest shared light node, so that the merges run once and a
-// scatter pass replaces the filling pass.  One thread per slot t: the light node w with
-// noff[w] <= t < noff[w + 1] (a binary search), then the members a < b of
-// E_w with t - noff[w] = b (b - 1) / 2 + a, merged as in k_light_pairs.  A
-// node's C(|E_w|, 2) merges are spread over as many threads, where the
-// one-wave-per-node kernel leaves the largest light node's wave running
-// long after the others.
+// The hyperedges of every light node, longest line-graph row first (ties: the
+// smaller id): of two of them the earlier owns the pair.  One thread per
+// incidence, which takes the place that its rank among the node's gives.
+__global__ __launch_bounds__(256) void k_sort_members(int64_t nnz, int64_t V, const int64_t* __restrict__ node_ptr,
+                                                      const int32_t* __restrict__ node_edges,
+                                                      const int8_t* __restrict__ heavy_bit,
+                                                      const int64_t* __restrict__ lg_ptr, int32_t* sorted) {
+  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (t >= nnz) return;
+  int64_t lo = 0, hi = V;  // node_ptr[lo] <= t < node_ptr[lo + 1]
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (node_ptr[mid] <= t) lo = mid; else hi = mid;
+  }
+  if (heavy_bit[lo] >= 0) return;
+  const int32_t y = node_edges[t];
+  const int64_t d = lg_ptr[y + 1] - lg_ptr[y], q0 = node_ptr[lo], q1 = node_ptr[lo + 1];
+  int rank = 0;
+  for (int64_t q = q0; q < q1; ++q) {
+    const int32_t x = node_edges[q];
+    const int64_t dx = lg_ptr[x + 1] - lg_ptr[x];
+    rank += dx > d || (dx == d && x < y) ? 1 : 0;
+  }
+  sorted[q0 + rank] = y;
+}
+
+// The flat list of candidate pairs, in units of kOwners slots: a light node w's
+// hyperedges y_0, y_1, ... (as sorted above), owners a in [kOwners c, kOwners
+// (c + 1)) and partner b > kOwners c, partners of one chunk c of owners in
+// turn.  A slot holds (owner, partner), or (-1, -1) where a >= b or w is not
+// the pair's smallest shared light node.
+constexpr int kOwners = 4;
+// Units before chunk c of a node of D hyperedges; the node's units.
+__host__ __device__ __forceinline__ int64_t unit_offset(int64_t c, int64_t D) {
+  return c * (D - 1) - kOwners * (c * (c - 1) / 2);
+}
+__host__ __device__ __forceinline__ int64_t node_units(int64_t D) {
+  return D < 2 ? 0 : unit_offset((D - 1 + kOwners - 1) / kOwners, D);
+}
+
+// One thread per slot t: the light node w with noff[w] <= t < noff[w + 1] (a
+// binary search), then the chunk and partner of its unit, merged as in
+// k_light_pairs.  A node's merges are spread over as many threads, where the
+// one-wave-per-node kernel leaves the largest light node's wave running long
+// after the others.
 __global__ __launch_bounds__(256) void k_light_slots(
-    int64_t V, int64_t ncand, const int64_t* __restrict__ node_ptr, const int32_t* __restrict__ node_edges,
+    int64_t V, int64_t ncand, const int64_t* __restrict__ node_ptr, const int32_t* __restrict__ sorted,
     const int8_t* __restrict__ heavy_bit, const int64_t* __restrict__ edge_ptr,
-    const int32_t* __restrict__ edge_nodes, const int64_t* __restrict__ lg_ptr,
-    unsigned long long* pcount, const int64_t* __restrict__ noff, int2* flat) {
+    const int32_t* __restrict__ edge_nodes, unsigned long long* pcount, const int64_t* __restrict__ noff,
+    int2* flat) {
   const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (t >= ncand) return;
   int64_t lo = 0, hi = V;  // largest w with noff[w] <= t (noff is nondecreasing, noff[V] = ncand > t)
@@ -112,38 +151,33 @@ __global__ __launch_bounds__(256) void k_light_slots(
     const int64_t mid = (lo + hi) >> 1;
     if (noff[mid] <= t) lo = mid; else hi = mid;
   }
-  const int64_t w = lo;
-  const int64_t r = t - noff[w];
-  // b (b - 1) / 2 <= r < b (b + 1) / 2
-  int64_t b = int64_t((1.0 + sqrt(1.0 + 8.0 * double(r))) * 0.5);
-  while (b * (b - 1) / 2 > r) --b;
-  while ((b + 1) * b / 2 <= r) ++b;
-  const int64_t a = r - b * (b - 1) / 2;
-  const int64_t base = node_ptr[w];
-  const int32_t ya = node_edges[base + a], yb = node_edges[base + b];
-  if (!smallest_shared_light(ya, yb, int32_t(w), edge_ptr, edge_nodes, heavy_bit)) {
-    flat[t] = make_int2(-1, -1);
-    return;
+  const int64_t w = lo, base = node_ptr[w], D = node_ptr[w + 1] - base;
+  const int64_t u = (t - noff[w]) / kOwners;
+  int64_t c0 = 0, c1 = (D - 1 + kOwners - 1) / kOwners;  // unit_offset(c0) <= u < unit_offset(c1)
+  while (c1 - c0 > 1) {
+    const int64_t mid = (c0 + c1) >> 1;
+    if (unit_offset(mid, D) <= u) c0 = mid; else c1 = mid;
   }
-  const int64_t da = lg_ptr[ya + 1] - lg_ptr[ya], db = lg_ptr[yb + 1] - lg_ptr[yb];
-  const bool a_owns = da > db || (da == db && ya < yb);
-  const int32_t owner = a_owns ? ya : yb, partner = a_owns ? yb : ya;
-  atomicAdd(&pcount[owner], 1ull);
-  flat[t] = make_int2(owner, partner);
+  const int64_t b = u - unit_offset(c0, D) + kOwners * c0 + 1;
+  const int64_t a = kOwners * c0 + (t - noff[w]) % kOwners;
+  int2 v = make_int2(-1, -1);
+  if (a < b) {
+    const int32_t ya = sorted[base + a], yb = sorted[base + b];
+    if (smallest_shared_light(ya, yb, int32_t(w), edge_ptr, edge_nodes, heavy_bit)) {
+      v = make_int2(ya, yb);
+      if (pcount) atomicAdd(&pcount[ya], 1ull);
+    }
+  }
+  flat[t] = v;
 }
 
-// Candidate pairs C(|E_w|, 2) of every light node (0 for heavy ones), the
-// input of the flat list's offsets; cnt[V] = 0.
+// Slots of every light node's units (0 for heavy ones), the input of the flat
+// list's offsets; cnt[V] = 0.
 __global__ void k_pair_slots(int64_t V, const int64_t* __restrict__ node_ptr,
                              const int8_t* __restrict__ heavy_bit, int64_t* cnt) {
   const int64_t w = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (w > V) return;
-  int64_t c = 0;
-  if (w < V && heavy_bit[w] < 0) {
-    const int64_t d = node_ptr[w + 1] - node_ptr[w];
-    c = d * (d - 1) / 2;
-  }
-  cnt[w] = c;
+  cnt[w] = w < V && heavy_bit[w] < 0 ? kOwners * node_units(node_ptr[w + 1] - node_ptr[w]) : 0;
 }
 
 // The flat list's pairs into each owner's partner range (cursor[] from zero).
@@ -338,10 +372,10 @@ __global__ __launch_bounds__(kFixThreads) __attribute__((amdgpu_waves_per_eu(8))
       for (int u = 0; u < kUnroll; ++u) {
         // wave-uniform tallies (a ballot counts the lanes still scanning)
         n_centres += uint32_t(__popcll(__ballot(hit[u])));
-        if (!hit[u]) continue;
         const uint32_t ls = __popc(Lk & ~mki[u]);
-        n_changed += uint32_t(__popcll(__ballot(ls != 0u)));
-        if (ls == 0u) continue;  // the pair kernel was exact at this centre
+        const bool fix = hit[u] && ls != 0u;  // otherwise the pair kernel was exact at this centre
+        n_changed += uint32_t(__popcll(__ballot(fix)));
+        if (!fix) continue;
         const int32_t i = iv[u];
         const uint32_t wik = __popc(mki[u]);
         const uint32_t t = __popc(mki[u] & mkj);
@@ -368,6 +402,313 @@ __global__ __launch_bounds__(kFixThreads) __attribute__((amdgpu_waves_per_eu(8))
     unsigned long long v = 0;
     for (int c = 0; c < kFixCopies; ++c) v += hist[c * kHistSlots + t];
     if (v) atomicAdd(&hist_out[int64_t(gj) * kHistSlots + t], v);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The same from a table of overlaps, W[j][i] = |e_j ∩ e_i| as a byte (0: not
+// neighbours): it answers at once whether a scanned entry is a centre and what
+// the owner's overlap with it is, with no bitmap of the owner's row to build.
+// So the pairs need no grouping by owner: the flat list is taken as it stands.
+// A wave takes a unit of it (up to kOwners owners with one partner) and
+// scans the partner's row once for all of them.  Columns of W are the centres
+// of the range.
+constexpr int kDenseThreads = 512;
+// Where the rows of W are long (kLongStride bytes), the waves of an XCD pull
+// kDensePull units at a time from a queue of its own, so that they are at few
+// owners together and those rows stay in its L2 (with 128 units per block the
+// blocks of an XCD are at 200 owners, 78 % of the reads miss and medium takes
+// 77 ms instead of 53).  Where they are short, a block takes kBlockUnits of a
+// queue and deals them out in LDS: a unit is then little work, and a global
+// atomic for each would cost as much (65 graphs of 6k hyperedges: 4 ms, 10 with
+// an atomic per unit).
+constexpr int kLongStride = 32768;
+constexpr int kDensePull = 2;
+constexpr uint32_t kBlockUnits = 64;
+constexpr int64_t kXcdUnits = 65536;  // by waves, a graph of as many units has a queue per XCD
+constexpr int kDenseCopies = 4;
+constexpr uint32_t kDenseFlush = 1u << 24;  // entries of a wave between flushes (8 waves share a counter)
+constexpr int kOverlapChunk = 32768;  // bytes of a row formed in LDS at a time
+
+// Per graph: where its rows of W start, their stride (a multiple of 16) and
+// the first centre; one thread per graph.
+struct OverlapTable {
+  int64_t off;
+  int32_t first, width, stride;
+};
+__device__ __forceinline__ OverlapTable overlap_of(int64_t e0, int64_t e1, int64_t c0, int64_t c1) {
+  OverlapTable t;
+  t.off = 0;
+  const int64_t lo = min(max(e0, c0), e1), hi = max(min(e1, c1), lo);
+  t.first = int32_t(lo);
+  t.width = int32_t(hi - lo);
+  t.stride = (t.width + 15) & ~15;
+  return t;
+}
+__global__ void k_overlap_offsets(int ng, const int64_t* __restrict__ geoff, int64_t c0, int64_t c1,
+                                  OverlapTable* tab) {
+  int64_t at = 0;
+  for (int g = 0; g < ng; ++g) {
+    OverlapTable t = overlap_of(geoff[g], geoff[g + 1], c0, c1);
+    t.off = at;
+    at += (geoff[g + 1] - geoff[g]) * t.stride;
+    tab[g] = t;
+  }
+}
+
+// One block per row: the row's bytes, kOverlapChunk at a time, from LDS.
+__global__ __launch_bounds__(256) void k_overlap_rows(const int32_t* __restrict__ row_graph,
+                                                      const int64_t* __restrict__ geoff,
+                                                      const OverlapTable* __restrict__ tab,
+                                                      const int64_t* __restrict__ lg_ptr,
+                                                      const int32_t* __restrict__ lg_col,
+                                                      const uint16_t* __restrict__ rsz, uint8_t* W) {
+  __shared__ uint4 buf[kOverlapChunk / 16];
+  uint8_t* bytes = reinterpret_cast<uint8_t*>(buf);
+  const int64_t i = blockIdx.x;
+  const int g = row_graph[i];
+  const OverlapTable t = tab[g];
+  uint8_t* out = W + t.off + (i - geoff[g]) * t.stride;
+  const int64_t base = lg_ptr[i];
+  const int d = int(lg_ptr[i + 1] - base);
+  const int lane = int(threadIdx.x) & (kWave - 1);
+  for (int x0 = 0; x0 < t.stride; x0 += kOverlapChunk) {
+    const int n16 = min(t.stride - x0, kOverlapChunk) / 16;
+    for (int x = threadIdx.x; x < n16; x += blockDim.x) buf[x] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    const int p0 = row_lower(lg_col + base, d, int64_t(t.first) + x0, lane);
+    const int p1 = row_lower(lg_col + base, d, int64_t(t.first) + min(x0 + kOverlapChunk, t.width), lane);
+    for (int p = p0 + int(threadIdx.x); p < p1; p += blockDim.x)
+      bytes[lg_col[base + p] - t.first - x0] = uint8_t(rsz[base + p] & 0xffu);
+    __syncthreads();
+    for (int x = threadIdx.x; x < n16; x += blockDim.x) reinterpret_cast<uint4*>(out + x0)[x] = buf[x];
+    __syncthreads();
+  }
+}
+
+// 6 waves per SIMD: 80 registers hold the owners' masks (at 8 waves some spill,
+// 57 ms on medium against 53), and two entries per lane in flight for each of
+// four owners.  What bounds it then is vector issue: 50 instructions per 64
+// entries and owner, 1.3e9 such (3.4e10 entries of 4.4e6 units on medium).
+__global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_light_dense(
+    int64_t c0, int64_t c1, int ng, uint32_t* queues, const int64_t* __restrict__ noff, const int2* __restrict__ flat,
+    const int64_t* __restrict__ geoff, const int64_t* __restrict__ gvoff, const OverlapTable* __restrict__ tab,
+    const uint8_t* __restrict__ W, const int64_t* __restrict__ edge_ptr, const int32_t* __restrict__ edge_nodes,
+    const int8_t* __restrict__ heavy_bit, const int64_t* __restrict__ lg_ptr, const int32_t* __restrict__ lg_col,
+    const int32_t* __restrict__ up_first, const uint32_t* __restrict__ recm, const uint16_t* __restrict__ rsz,
+    const uint16_t* __restrict__ code_to_id3, unsigned long long* hist_out, unsigned long long* tally) {
+  __shared__ uint16_t lut[kNumCodes];              // by reversed code: word of the id in a histogram copy
+  __shared__ int32_t hist[kDenseCopies * kGStride];
+  __shared__ unsigned long long s_tally[3];        // entries scanned, centres examined, centres reclassified
+  __shared__ uint32_t s_taken[2], s_base, s_next;
+  for (int t = threadIdx.x; t < kNumCodes; t += blockDim.x) lut[t] = uint16_t(code_to_id3[kNumCodes - 1 - t] * 4u);
+  for (int t = threadIdx.x; t < kDenseCopies * kGStride; t += blockDim.x) hist[t] = 0;
+  if (threadIdx.x < 3) s_tally[threadIdx.x] = 0ull;
+  const int lane = int(threadIdx.x) & (kWave - 1);
+  char* myhist = reinterpret_cast<char*>(hist + (lane & (kDenseCopies - 1)) * kGStride);
+  unsigned long long n_scanned = 0, n_centres = 0, n_changed = 0;  // this wave's, for mochy_exact_stats
+  uint32_t unflushed = 0;  // entries this wave scanned since it last emptied the histogram
+  const int first = int(int64_t(blockIdx.x) * ng / gridDim.x);
+  for (int v = 0; v < ng; ++v) {  // every graph, each block from a share of its own
+    const int g = first + v < ng ? first + v : first + v - ng;
+    const int64_t slot0 = noff[gvoff[g]];
+    const uint32_t units = uint32_t((noff[gvoff[g + 1]] - slot0) / kOwners);
+    const OverlapTable t = tab[g];
+    const bool by_wave = t.stride >= kLongStride;
+    const uint32_t nq = by_wave && units >= kXcdUnits ? kXcds : 1u, per = (units + nq - 1u) / nq;
+    const uint32_t bunits = 
+        uint32_t(min(max(int64_t(units) * ng / (gridDim.x * 2), int64_t(kDenseThreads / kWave)), int64_t(kBlockUnits)));
+    uint32_t* queue = queues + size_t(g) * kXcds;
+    if (threadIdx.x == 0)
+      s_taken[v & 1] = nq > 1u ? 0u : __hip_atomic_load(queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (uint32_t(uniform(int(s_taken[v & 1]))) >= units) continue;
+    const int64_t e0 = geoff[g], e1 = geoff[g + 1];
+    uint32_t turn = 0, at = 0, stop = 0;  // by wave: queues tried; units in hand
+    uint32_t base = 0, end = 0;           // by block: units in hand
+    for (;;) {
+      if (by_wave) {
+        if (at == stop) {
+          const uint32_t x = (blockIdx.x + turn) % nq;
+          int got = 0;
+          if (lane == 0) got = int(atomicAdd(&queue[x], uint32_t(kDensePull)));
+          at = uint32_t(uniform(got));
+          const uint32_t last = min(per, units - min(units, x * per));  // units of this queue
+          if (at >= last) {
+            stop = at;
+            if (++turn == nq) break;
+            continue;
+          }
+          stop = min(at + uint32_t(kDensePull), last) + x * per;
+          at += x * per;
+        }
+      } else {
+        int got = 0;
+        if (base < end && lane == 0) got = int(atomicAdd(&s_next, 1u));
+        at = base + uint32_t(uniform(got));
+        if (at >= end) {  // every wave of the block comes here once per share
+          __syncthreads();
+          if (threadIdx.x == 0) {
+            s_base = atomicAdd(queue, bunits);
+            s_next = 0u;
+          }
+          __syncthreads();
+          base = uint32_t(uniform(int(s_base)));
+          end = min(base + bunits, units);
+          if (base >= units) break;
+          continue;
+        }
+      }
+      if (unflushed >= kDenseFlush) {  // keeps the 32-bit counters of the block far from their ends
+        for (int q = lane; q < kDenseCopies * kGStride; q += kWave) {
+          const int32_t n = atomicExch(&hist[q], 0);
+          if (n) atomicAdd(&hist_out[int64_t(g) * kHistSlots + q % kGStride], (unsigned long long)int64_t(n));
+        }
+        n_scanned += unflushed;
+        unflushed = 0;
+      }
+      const int64_t slot = slot0 + int64_t(at++) * kOwners;
+      // The unit's owners side by side, 16 lanes each (the work before the scan
+      // is a chain of dependent loads, so it is done once for all of them).
+      const int part = lane & 48, sub = lane & 15;
+      const int2 pr = flat[slot + (lane >> 4)];
+      const unsigned long long valid = __ballot(pr.x >= 0);
+      if (valid == 0ull) continue;
+      const int32_t k = __builtin_amdgcn_readlane(pr.y, __builtin_ctzll(valid));
+      const int32_t j = pr.x >= 0 ? pr.x : k;
+      const int64_t kn0 = edge_ptr[k], kb = lg_ptr[k], jn0 = edge_ptr[j];
+      const uint32_t sizek = uint32_t(edge_ptr[k + 1] - kn0), sizej = uint32_t(edge_ptr[j + 1] - jn0);
+      const int d = int(lg_ptr[k + 1] - kb);
+      const int32_t vk = uint32_t(lane) < sizek ? edge_nodes[kn0 + lane] : -1;
+      const int32_t vj0 = uint32_t(sub) < sizej ? edge_nodes[jn0 + sub] : -2;
+      const int32_t vj1 = uint32_t(sub) + 16u < sizej ? edge_nodes[jn0 + sub + 16] : -2;
+      const uint32_t heavy = uint32_t(__ballot(vk >= 0 && heavy_bit[max(vk, 0)] >= 0));
+      // masks over e_k's nodes: e_j ∩ e_k (mkj), its heavy and light nodes
+      uint32_t mkj = 0;
+      for (uint32_t q = 0; q < sizek; ++q) {
+        const int32_t node = __builtin_amdgcn_readlane(vk, int(q));
+        const unsigned long long eq = __ballot(vj0 == node || vj1 == node);
+        mkj |= ((eq >> part) & 0xffffull) != 0ull ? 1u << q : 0u;
+      }
+      if (pr.x < 0) mkj = 0u;
+      const uint32_t Hk = mkj & heavy, Lk = mkj & ~heavy;
+      // The part of row k to scan: centres of [c0, c1) and, where e_j and e_k
+      // share a heavy node, those below both (see fix_range); 16 probes a step
+      const int32_t* row = lg_col + kb;
+      const int64_t i1 = Hk != 0u ? min(c1, int64_t(min(j, k))) : c1;
+      const int r_lo = c0 > e0 ? row_lower(row, d, c0, lane) : 0;
+      int hi = r_lo;
+      for (int n = i1 < e1 && pr.x >= 0 ? d - r_lo : 0; __ballot(n > 0) != 0ull;) {
+        const int step = (n + 15) / 16;
+        const int x = sub * step;
+        const unsigned long long less = __ballot(x < n && row[hi + x] < i1);
+        const int below = __popcll((less >> part) & 0xffffull);
+        n = below == 0 ? 0 : min(step - 1, n - ((below - 1) * step + 1));
+        if (below) hi += (below - 1) * step + 1;
+      }
+      if (i1 >= e1) hi = d;
+      if (pr.x < 0) hi = 0;
+      // per owner: the masks in vector registers (as scalars they are spilled)
+      const uint32_t wofs = uint32_t((j - e0) * (t.stride / 16));  // the owner's row of W, in 16 bytes
+      uint32_t mkj_o[kOwners], Hk_o[kOwners], Lk_o[kOwners];
+      uint32_t sizej_o[kOwners], wj[kOwners];
+      int32_t below_o[kOwners];
+      int hi_o[kOwners], r_hi = 0;
+#pragma unroll
+      for (int o = 0; o < kOwners; ++o) {
+        mkj_o[o] = uint32_t(__builtin_amdgcn_readlane(int(mkj), 16 * o));
+        Hk_o[o] = uint32_t(__builtin_amdgcn_readlane(int(Hk), 16 * o));
+        Lk_o[o] = uint32_t(__builtin_amdgcn_readlane(int(Lk), 16 * o));
+        asm volatile("" : "+v"(mkj_o[o]), "+v"(Hk_o[o]), "+v"(Lk_o[o]));
+        sizej_o[o] = uint32_t(__builtin_amdgcn_readlane(int(sizej), 16 * o));
+        wj[o] = uint32_t(__builtin_amdgcn_readlane(int(wofs), 16 * o));
+        below_o[o] = __builtin_amdgcn_readlane(min(j, k), 16 * o);
+        hi_o[o] = __builtin_amdgcn_readlane(hi, 16 * o);
+        r_hi = max(r_hi, hi_o[o]);
+        unflushed += uint32_t(max(hi_o[o] - r_lo, 0));
+      }
+      const uint8_t* wg = W + t.off - t.first;
+      // kUnroll entries of row k per lane at a time, the loads of one stage
+      // issued together, with no branch between them
+      constexpr int kUnroll = 2;
+      for (int r0 = r_lo + lane; r0 < r_hi; r0 += kUnroll * kWave) {
+        int32_t iv[kUnroll];
+        uint32_t mki[kUnroll], sz[kUnroll], pj[kOwners][kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          const int r = min(r0 + u * kWave, r_hi - 1);
+          iv[u] = lg_col[kb + r];
+          mki[u] = recm[kb + r];  // e_k ∩ e_i over e_k's nodes
+          sz[u] = rsz[kb + r];    // |e_k ∩ e_i| | |e_i| << 8
+        }
+#pragma unroll
+        for (int o = 0; o < kOwners; ++o)
+#pragma unroll
+          for (int u = 0; u < kUnroll; ++u) pj[o][u] = wg[int64_t(wj[o]) * 16 + iv[u]];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          const int r = r0 + u * kWave;
+          const uint32_t wik = sz[u] & 0xffu, a = sz[u] >> 8;
+          const uint32_t aks2 = 2u * (a - wik) - 4u;
+          const uint32_t kso = wik | ((sizek - wik) << 16);
+#pragma unroll
+          for (int o = 0; o < kOwners; ++o) {
+            const uint32_t p = pj[o][u];
+            const bool hit = p != 0u && r < hi_o[o];  // a neighbour of e_j (i == j never is)
+            n_centres += uint32_t(__popcll(__ballot(hit)));
+            const uint32_t ls = uint32_t(__popc(Lk_o[o] & ~mki[u]));
+            const bool fix = hit && ls != 0u;  // otherwise the pair kernel was exact at this centre
+            n_changed += uint32_t(__popcll(__ballot(fix)));
+            if (!fix) continue;
+            const uint32_t t2 = uint32_t(__popc(mki[u] & mkj_o[o])) + 2u;
+            const uint32_t r5h2 = uint32_t(__popc(Hk_o[o] & ~mki[u])) + 2u;
+            const uint32_t jy = p | ((2u * p + 4u) << 8) | ((sizej_o[o] - p) << 16);
+            const uint32_t tr = t2 | (r5h2 << 16);
+            const bool above = iv[u] < below_o[o];
+            if (above || tr == 0x00020002u)
+              atomicAdd(reinterpret_cast<int32_t*>(myhist + lut_at(lut, pair_rcode2(t2, tr, aks2, jy, kso))), -1);
+            if (above)
+              atomicAdd(
+                  reinterpret_cast<int32_t*>(myhist + lut_at(lut, pair_rcode2(t2, tr + (ls << 16), aks2, jy, kso))), 1);
+          }
+        }
+      }
+    }
+    n_scanned += unflushed;
+    unflushed = 0;
+    __syncthreads();
+    for (int q = threadIdx.x; q < kHistSlots; q += blockDim.x) {
+      int64_t v = 0;
+      for (int c = 0; c < kDenseCopies; ++c) {
+        v += hist[c * kGStride + q];
+        hist[c * kGStride + q] = 0;
+      }
+      if (v) atomicAdd(&hist_out[int64_t(g) * kHistSlots + q], (unsigned long long)v);
+    }
+    __syncthreads();
+  }
+  if (lane == 0 && n_scanned != 0u) {
+    atomicAdd(&s_tally[0], (unsigned long long)n_scanned);
+    atomicAdd(&s_tally[1], (unsigned long long)n_centres);
+    atomicAdd(&s_tally[2], (unsigned long long)n_changed);
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) tally[blockIdx.x * 3 + threadIdx.x] = s_tally[threadIdx.x];  // summed by k_fix_tally
+}
+
+// Valid slots of the flat list (light pairs), for mochy_exact_stats.
+__global__ __launch_bounds__(256) void k_count_pairs(int64_t n, const int2* __restrict__ flat,
+                                                     unsigned long long* stats) {
+  __shared__ unsigned long long red[256 / kWave];
+  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+  unsigned long long v = 0;
+  for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < n; t += stride) v += flat[t].x >= 0 ? 1u : 0u;
+  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+  if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    v = red[0] + red[1] + red[2] + red[3];
+    if (v) atomicAdd(&stats[kStLightPairs], v);
   }
 }
 
@@ -447,9 +788,11 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
   int32_t* item_owner = nullptr;
   unsigned long long* tally = nullptr;
   int64_t* noff = nullptr;
+  int32_t* sorted = nullptr;
   int2* flat = nullptr;
   auto done = [&](mochy_status s) {
     device_free(ctx, noff);
+    device_free(ctx, sorted);
     device_free(ctx, flat);
     device_free(ctx, buf);
     device_free(ctx, eoff);
@@ -482,15 +825,64 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
     MOCHY_HIP_OR(hipStreamSynchronize(st), done);
     ncand = ctx->h_small[503];
     if (ncand > 0 && size_t(ncand) * 8 <= kFlatBytes &&
-        device_alloc(ctx, (void**)&flat, size_t(ncand) * 8) != MOCHY_OK) {
-      (void)hipGetLastError();  // no room for the list: the two passes instead
-      flat = nullptr;
+        (device_alloc(ctx, (void**)&sorted, size_t(g->nnz) * 4) != MOCHY_OK ||
+         device_alloc(ctx, (void**)&flat, size_t(ncand) * 8) != MOCHY_OK)) {
+      flat = nullptr;  // no room for the list: the two passes instead
+      ctx->err.clear();
+    }
+    if (flat)
+      k_sort_members<<<blocks(g->nnz, 256), 256, 0, st>>>(g->nnz, V, g->node_ptr, g->node_edges, g->heavy_bit,
+                                                          g->lg_ptr, sorted);
+  }
+  // the overlap table where it takes at most a sixth of the device memory
+  // (40 GB for the largest graph) and can be allocated
+  uint8_t* W = nullptr;
+  OverlapTable* tab = nullptr;
+  if (flat) {
+    size_t wbytes = 0;
+    for (int x = 0; x < g->ng; ++x) {
+      const int64_t e0 = g->h_geoff[x], e1 = g->h_geoff[x + 1];
+      const int64_t width = std::max<int64_t>(std::min(e1, c1) - std::max(e0, c0), 0);
+      wbytes += size_t(e1 - e0) * size_t((width + 15) & ~int64_t(15));
+    }
+    if (wbytes > 0 && wbytes <= size_t(ctx->total_mem / 6) &&
+        (device_alloc(ctx, (void**)&tab, size_t(g->ng) * sizeof(OverlapTable)) != MOCHY_OK ||
+         device_alloc(ctx, (void**)&W, wbytes) != MOCHY_OK)) {
+      device_free(ctx, tab);  // no room: owner by owner instead
+      tab = nullptr;
+      W = nullptr;
+      ctx->err.clear();
     }
   }
+  if (W) {
+    const int64_t nblocks = std::min<int64_t>(int64_t(ctx->num_cus) * 4, (ncand + 4 * kOwners - 1) / (4 * kOwners));
+    uint32_t* queues = nullptr;
+    auto dense_done = [&](mochy_status s) {
+      device_free(ctx, W);
+      device_free(ctx, tab);
+      return done(s);
+    };
+    const size_t qbytes = size_t(g->ng) * kXcds * 4;
+    if ((rc = device_alloc(ctx, (void**)&tally, size_t(nblocks) * 24 + qbytes)) != MOCHY_OK) return dense_done(rc);
+    queues = (uint32_t*)(tally + nblocks * 3);
+    launch_fill_u32(queues, 0u, qbytes, st);
+    k_light_slots<<<blocks(ncand, 256), 256, 0, st>>>(V, ncand, g->node_ptr, sorted, g->heavy_bit, g->edge_ptr,
+                                                      g->edge_nodes, nullptr, noff, flat);
+    k_overlap_offsets<<<1, 1, 0, st>>>(g->ng, g->geoff, c0, c1, tab);
+    k_overlap_rows<<<unsigned(E), 256, 0, st>>>(g->row_graph, g->geoff, tab, g->lg_ptr, g->lg_col, g->rsz, W);
+    phase_begin(ctx, kPhFix);
+    k_light_dense<<<unsigned(nblocks), kDenseThreads, 0, st>>>(
+        c0, c1, g->ng, queues, noff, flat, g->geoff, g->gvoff, tab, W, g->edge_ptr, g->edge_nodes, g->heavy_bit,
+        g->lg_ptr, g->lg_col, g->up_first, g->recm, g->rsz, ctx->d_code_to_id3, (unsigned long long*)d_hist, tally);
+    phase_end(ctx, kPhFix);
+    k_fix_tally<<<kTallyBlocks, 256, 0, st>>>(nblocks, tally, stats);
+    k_count_pairs<<<unsigned(std::min<int64_t>(blocks(ncand, 256), 256)), 256, 0, st>>>(ncand, flat, stats);
+    MOCHY_HIP_OR(hipGetLastError(), dense_done);
+    return dense_done(MOCHY_OK);
+  }
   if (flat)
-    k_light_slots<<<unsigned(blocks(ncand, 256)), 256, 0, st>>>(V, ncand, g->node_ptr, g->node_edges,
-                                                              g->heavy_bit, g->edge_ptr, g->edge_nodes,
-                                                              g->lg_ptr, pcount, noff, flat);
+    k_light_slots<<<blocks(ncand, 256), 256, 0, st>>>(V, ncand, g->node_ptr, sorted, g->heavy_bit, g->edge_ptr,
+                                                      g->edge_nodes, pcount, noff, flat);
   else
     k_light_pairs<kCount><<<wblocks, 256, 0, st>>>(V, g->node_ptr, g->node_edges, g->heavy_bit,
                                                    g->edge_ptr, g->edge_nodes, g->lg_ptr, pcount,
