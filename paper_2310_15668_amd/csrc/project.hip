@@ -7,10 +7,11 @@
 //   3. pick the 64 highest-degree nodes ("heavy"; ties to the smaller id);
 //   4. line-graph degree of every hyperedge: the row of e_i is the union of
 //      E_v over v in e_i minus e_i itself, formed as a bitmap over hyperedge
-//      ids in LDS (so the row comes out sorted and de-duplicated);
+//      ids in LDS (so the row comes out sorted and de-duplicated), from bitmaps
+//      of the heavy nodes' lists and the other lists' hyperedges;
 //   5. scan the degrees into row pointers; |wedges| = sum / 2;
-//   6. fill the rows (ascending neighbour ids) from the same bitmap;
-//   7. one 16-byte record per (centre, neighbour): which nodes of e_i the
+//   6. fill the rows (ascending neighbour ids) from the same bitmap, with one
+//      16-byte record per (centre, neighbour): which nodes of e_i the
 //      neighbour holds (a 32-bit mask; omega = its popcount), how many of its
 //      nodes lie outside e_i, which heavy nodes lie outside e_i, and whether a
 //      non-heavy node does.  Identical hyperedges show up here (no outside
@@ -159,151 +160,231 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy(const int64_t* __restri
   }
 }
 
+// What a row's records need of each hyperedge: its heavy nodes as a mask (bit
+// heavy_bit[v]) and its size; and the heavy nodes' lists as bitmaps over all
+// hyperedges (heavy index b of its own graph: row b), one wave turning 64 masks
+// over at a time.
+struct EdgeInfo {
+  unsigned long long heavy;
+  uint32_t size, pad;
+};
+
+__host__ __device__ constexpr int64_t heavy_words(int64_t E) { return (E + 63) / 64 + 1; }  // 64-bit, one to spare
+
+__global__ __launch_bounds__(256) void k_edge_heavy(int64_t E, const int64_t* __restrict__ ptr,
+                                                    const int32_t* __restrict__ nodes,
+                                                    const int8_t* __restrict__ heavy_bit, EdgeInfo* info,
+                                                    unsigned long long* rows) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t nw = heavy_words(E), w = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
+  if (w >= nw) return;  // whole wave
+  const int64_t x = w * 64 + lane;
+  unsigned long long h = 0;
+  if (x < E) {
+    const int64_t s = ptr[x], e = ptr[x + 1];
+    for (int64_t q = s; q < e; ++q) {
+      const int b = heavy_bit[nodes[q]];
+      if (b >= 0) h |= 1ull << b;
+    }
+    info[x] = EdgeInfo{h, uint32_t(e - s), 0u};
+  }
+  unsigned long long mine = 0;
+  for (int b = 0; b < kHeavyBits; ++b) {
+    const unsigned long long row = __ballot((h >> b) & 1ull);
+    if (lane == b) mine = row;
+  }
+  rows[lane * nw + w] = mine;
+}
+
+// The nodes of e_i by how their lists enter the row's bitmap: as the heavy
+// node's bitmap, or hyperedge by hyperedge.
+struct RowNodes {
+  int32_t ei[MOCHY_MAX_EDGE];
+  int8_t hbit[MOCHY_MAX_EDGE], hpos[MOCHY_MAX_EDGE];  // heavy nodes: heavy index, position in e_i
+  int8_t dense[MOCHY_MAX_EDGE];                       // heavy index of each list taken as a bitmap
+  int64_t lo[MOCHY_MAX_EDGE], hi[MOCHY_MAX_EDGE];     // the other lists
+  bool light[MOCHY_MAX_EDGE];
+  int a, nh, nd, nl;
+};
+
+// A heavy list is taken as a bitmap if that is no more than kWalkWords words
+// for each of its hyperedges: a word costs a load of 4 bytes in order (two
+// where the graph's first hyperedge is not the first bit of one), a hyperedge
+// its load and one or two LDS atomics at random.
+constexpr int kWalkWords = 8;
+
 // Builds the neighbour bitmap of row i in LDS: bit x - e0 for neighbour x,
-// where the row's graph owns hyperedges [e0, e0 + 32 * nwords).
-__device__ void build_row_bitmap(int64_t i, int64_t e0, const int64_t* __restrict__ ptr,
-                                 const int32_t* __restrict__ nodes,
-                                 const int64_t* __restrict__ node_ptr,
-                                 const int32_t* __restrict__ node_edges, uint32_t* bm, int nwords) {
-  for (int w = threadIdx.x; w < nwords; w += blockDim.x) bm[w] = 0;
-  __syncthreads();
-  for (int64_t q = ptr[i]; q < ptr[i + 1]; ++q) {
-    const int32_t v = nodes[q];
-    const int64_t lo = node_ptr[v], hi = node_ptr[v + 1];
-    for (int64_t r = lo + threadIdx.x; r < hi; r += blockDim.x) {
-      const int64_t x = node_edges[r];
-      if (x != i) atomicOr(&bm[(x - e0) >> 5], 1u << ((x - e0) & 31));
+// where the row's graph owns hyperedges [e0, e1), nwords words.  kLight: also
+// the bitmap of those sharing a light node with e_i.  (i's own bit is 0.)
+template <bool kLight>
+__device__ void build_row_bitmap(int64_t i, int64_t e0, int64_t e1, int64_t E, const int64_t* __restrict__ ptr,
+                                 const int32_t* __restrict__ nodes, const int64_t* __restrict__ node_ptr,
+                                 const int32_t* __restrict__ node_edges, const int8_t* __restrict__ heavy_bit,
+                                 const unsigned long long* __restrict__ hrows, RowNodes& rn, uint32_t* bm,
+                                 uint32_t* light, int nwords) {
+  const int64_t s = ptr[i];
+  const int a = int(ptr[i + 1] - s);
+  if (threadIdx.x < unsigned(kWave)) {  // the first wave sorts the nodes out
+    const int lane = threadIdx.x;
+    int32_t v = -1;
+    int hb = -1;
+    int64_t lo = 0, hi = 0;
+    if (lane < a) {
+      v = nodes[s + lane];
+      hb = heavy_bit[v];
+      lo = node_ptr[v];
+      hi = node_ptr[v + 1];
+      rn.ei[lane] = v;
+    }
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const unsigned long long heavy = __ballot(hb >= 0);
+    const unsigned long long dense = __ballot(hb >= 0 && (hi - lo) * kWalkWords >= nwords);
+    const unsigned long long walk = __ballot(lane < a && hi - lo > 1) & ~dense;
+    if ((heavy >> lane) & 1ull) {
+      const int at = __popcll(heavy & below);
+      rn.hbit[at] = int8_t(hb);
+      rn.hpos[at] = int8_t(lane);
+    }
+    if ((dense >> lane) & 1ull) rn.dense[__popcll(dense & below)] = int8_t(hb);
+    if ((walk >> lane) & 1ull) {
+      const int at = __popcll(walk & below);
+      rn.lo[at] = lo;
+      rn.hi[at] = hi;
+      rn.light[at] = hb < 0;
+    }
+    if (lane == 0) {
+      rn.a = a;
+      rn.nh = __popcll(heavy);
+      rn.nd = __popcll(dense);
+      rn.nl = __popcll(walk);
     }
   }
   __syncthreads();
+  const int nd = rn.nd, nl = rn.nl;
+  const int64_t stride = heavy_words(E) * 2;
+  const uint32_t* hw = reinterpret_cast<const uint32_t*>(hrows) + (e0 >> 5);
+  const int shift = int(e0 & 31);
+  const int last = nwords - 1;
+  const uint32_t tail = (e1 - e0) & 31 ? (1u << ((e1 - e0) & 31)) - 1u : ~0u;  // the last word's bits
+  for (int w = threadIdx.x; w < nwords; w += blockDim.x) {
+    uint32_t bits = 0;
+    for (int d = 0; d < nd; ++d) {
+      const uint32_t* row = hw + rn.dense[d] * stride + w;
+      uint32_t x = row[0] >> shift;
+      if (shift) x |= row[1] << (32 - shift);
+      bits |= x;
+    }
+    bm[w] = w == last ? bits & tail : bits;
+    if (kLight) light[w] = 0u;
+  }
+  __syncthreads();
+  for (int l = 0; l < nl; ++l) {
+    const int64_t hi = rn.hi[l];
+    const bool is_light = rn.light[l];
+    for (int64_t r = rn.lo[l] + threadIdx.x; r < hi; r += blockDim.x) {
+      const int64_t x = int64_t(node_edges[r]) - e0;
+      atomicOr(&bm[x >> 5], 1u << (x & 31));
+      if (kLight && is_light) atomicOr(&light[x >> 5], 1u << (x & 31));
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) bm[(i - e0) >> 5] &= ~(1u << ((i - e0) & 31));
+  __syncthreads();
 }
 
-__device__ __forceinline__ void graph_range(int64_t i, const int32_t* __restrict__ row_graph,
-                                            const int64_t* __restrict__ geoff, int64_t& e0,
-                                            int& nwords) {
-  const int gi = row_graph[i];
-  e0 = geoff[gi];
-  nwords = int((geoff[gi + 1] - e0 + 31) / 32);
+// Largest value to *most: few rows exceed what is there, and as many atomics on
+// one address as rows took four times as long as the rows (22,700 rows of 9
+// graphs: 266 us).
+__device__ __forceinline__ void note_max(int32_t* most, int32_t n) {
+  if (n > __hip_atomic_load(most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(most, n);
 }
 
 __global__ __launch_bounds__(256) void k_proj_degree(int64_t E, const int64_t* __restrict__ ptr,
                                                      const int32_t* __restrict__ nodes,
                                                      const int64_t* __restrict__ node_ptr,
                                                      const int32_t* __restrict__ node_edges,
+                                                     const int8_t* __restrict__ heavy_bit,
+                                                     const unsigned long long* __restrict__ hrows,
                                                      const int32_t* __restrict__ row_graph,
                                                      const int64_t* __restrict__ geoff,
                                                      int64_t* deg, int32_t* max_deg) {
   extern __shared__ uint32_t bm[];
-  __shared__ int32_t red[256];
+  __shared__ RowNodes rn;
+  __shared__ int32_t red[256 / kWave];
   const int64_t i = blockIdx.x;
-  int64_t e0;
-  int nwords;
-  graph_range(i, row_graph, geoff, e0, nwords);
-  build_row_bitmap(i, e0, ptr, nodes, node_ptr, node_edges, bm, nwords);
+  const int gi = row_graph[i];
+  const int64_t e0 = geoff[gi], e1 = geoff[gi + 1];
+  const int nwords = int((e1 - e0 + 31) / 32);
+  build_row_bitmap<false>(i, e0, e1, E, ptr, nodes, node_ptr, node_edges, heavy_bit, hrows, rn, bm, nullptr, nwords);
   int32_t c = 0;
   for (int w = threadIdx.x; w < nwords; w += blockDim.x) c += __popc(bm[w]);
-  red[threadIdx.x] = c;
+  for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = c;
   __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (threadIdx.x < unsigned(off)) red[threadIdx.x] += red[threadIdx.x + off];
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
-    deg[i] = red[0];
-    atomicMax(max_deg, red[0]);
+    c = red[0] + red[1] + red[2] + red[3];
+    deg[i] = c;
+    note_max(max_deg, c);
   }
 }
 
-__global__ __launch_bounds__(256) void k_proj_fill(int64_t E, const int64_t* __restrict__ ptr,
-                                                   const int32_t* __restrict__ nodes,
-                                                   const int64_t* __restrict__ node_ptr,
-                                                   const int32_t* __restrict__ node_edges,
-                                                   const int32_t* __restrict__ row_graph,
-                                                   const int64_t* __restrict__ geoff,
-                                                   const int64_t* __restrict__ lg_ptr,
-                                                   int32_t* lg_col, int32_t* up_first) {
+// Row i of the line graph and its records, a block to a row.  The row's bitmap
+// is turned into sorted neighbours a tile of 256 words at a time, staged in LDS
+// so that the records are written in order; a neighbour's mask of e_i's heavy
+// nodes and its heavy outside nodes follow from its own heavy mask.  Those that
+// share a light node as well (1 to 3 of a hundred) need their nodes compared
+// with e_i's; they are put off until there is one for most threads.
+//
+// Bound by the latency of the tiles' steps and the 26 bytes written per entry
+// (2.4 TB/s).  8.7e8 entries of 85,357 rows: 9.4 ms, where a kernel for the rows
+// (4.1 ms, every list walked) was followed by one that compared every
+// neighbour's nodes (19.0 ms, 470 instructions for 64 entries); the same with 2
+// or 8 entries of a thread in flight, 512 threads to a block, or stores past the
+// caches.
+constexpr int kRowThreads = 256, kRowQueue = 512;
+constexpr int kRowUnroll = 4;
+
+__global__ __launch_bounds__(kRowThreads) void k_proj_rows(
+    int64_t E, const int64_t* __restrict__ ptr, const int32_t* __restrict__ nodes,
+    const int64_t* __restrict__ node_ptr, const int32_t* __restrict__ node_edges,
+    const int8_t* __restrict__ heavy_bit, const EdgeInfo* __restrict__ info,
+    const unsigned long long* __restrict__ hrows, const int32_t* __restrict__ row_graph,
+    const int64_t* __restrict__ geoff, const int64_t* __restrict__ lg_ptr, int32_t* lg_col, int32_t* up_first,
+    uint4* rec, uint32_t* recm, uint16_t* rsz, int32_t* flags) {
   extern __shared__ uint32_t bm[];
-  __shared__ int32_t part[256];
+  __shared__ RowNodes rn;
+  __shared__ uint16_t stage[kRowThreads * 32];  // bits of the tile that are set
+  __shared__ uint2 queue[kRowQueue];            // neighbour, position: put off
+  __shared__ uint32_t filt[32];  // membership filter of e_i's nodes by their low 10 bits
+  __shared__ uint32_t s_wave[kRowThreads / kWave], s_put;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int64_t i = blockIdx.x;
-  int64_t e0;
-  int nwords;
-  graph_range(i, row_graph, geoff, e0, nwords);
-  build_row_bitmap(i, e0, ptr, nodes, node_ptr, node_edges, bm, nwords);
-  // each thread owns a contiguous chunk of words
-  const int chunk = (nwords + 255) / 256;
-  const int w0 = min(nwords, int(threadIdx.x) * chunk), w1 = min(nwords, w0 + chunk);
-  int32_t c = 0;
-  for (int w = w0; w < w1; ++w) c += __popc(bm[w]);
-  part[threadIdx.x] = c;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const int32_t add = threadIdx.x >= unsigned(off) ? part[threadIdx.x - off] : 0;
-    __syncthreads();
-    part[threadIdx.x] += add;
-    __syncthreads();
-  }
-  int32_t pos = part[threadIdx.x] - c;  // exclusive
-  int32_t* out = lg_col + lg_ptr[i];
-  const int64_t il = i - e0;
-  const int wi = int(il >> 5);
-  for (int w = w0; w < w1; ++w) {
-    uint32_t bits = bm[w];
-    if (w == wi) up_first[i] = pos + __popc(bits & ((1u << (il & 31)) - 1u));
-    while (bits) {
-      const int b = __ffs(bits) - 1;
-      bits &= bits - 1;
-      out[pos++] = int32_t(e0 + ((w << 5) | b));
-    }
-  }
-}
-
-// Each hyperedge's heavy nodes as a 64-bit mask (bit heavy_bit[v]).
-__global__ void k_edge_heavy(int64_t E, const int64_t* __restrict__ ptr, const int32_t* __restrict__ nodes,
-                             const int8_t* __restrict__ heavy_bit, unsigned long long* hmask) {
-  const int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (x >= E) return;
-  unsigned long long h = 0;
-  for (int64_t q = ptr[x]; q < ptr[x + 1]; ++q) {
-    const int b = heavy_bit[nodes[q]];
-    if (b >= 0) h |= 1ull << b;
-  }
-  hmask[x] = h;
-}
-
-// Row i's records: for each neighbour e_x, the mask of e_i's nodes it holds
-// (found by scanning e_x's nodes against e_i), its outside count, and its
-// heavy outside nodes, hmask[x] less e_i's own heavy nodes.
-__global__ __launch_bounds__(256) void k_records(int64_t E, const int64_t* __restrict__ ptr,
-                                                 const int32_t* __restrict__ nodes,
-                                                 const unsigned long long* __restrict__ hmask,
-                                                 const int64_t* __restrict__ lg_ptr,
-                                                 const int32_t* __restrict__ lg_col, uint4* rec,
-                                                 uint32_t* recm, uint16_t* rsz, int32_t* flags) {
-  __shared__ int32_t ei[MOCHY_MAX_EDGE];
-  // membership filter of e_i's nodes by their low 10 bits: most nodes of a
-  // neighbour are outside e_i and leave after one read
-  __shared__ uint32_t filt[32];
-  const int64_t i = blockIdx.x;
-  const int64_t s = ptr[i];
-  const int a = int(ptr[i + 1] - s);
-  if (threadIdx.x < 32u) filt[threadIdx.x] = 0u;
-  __syncthreads();
-  if (threadIdx.x < unsigned(a)) {
-    const int32_t v = nodes[s + threadIdx.x];
-    ei[threadIdx.x] = v;
-    atomicOr(&filt[(v >> 5) & 31], 1u << (v & 31));
-  }
-  __syncthreads();
+  const int gi = row_graph[i];
+  const int64_t e0 = geoff[gi], e1 = geoff[gi + 1], il = i - e0;
+  const int nwords = int((e1 - e0 + 31) / 32);
+  uint32_t* light = bm + nwords;
+  if (tid < 32) filt[tid] = 0u;
+  if (tid == 0) s_put = 0u;
+  build_row_bitmap<true>(i, e0, e1, E, ptr, nodes, node_ptr, node_edges, heavy_bit, hrows, rn, bm, light, nwords);
+  const int a = rn.a, nh = rn.nh;
+  if (tid < a) atomicOr(&filt[(rn.ei[tid] >> 5) & 31], 1u << (rn.ei[tid] & 31));
   const int64_t base = lg_ptr[i];
-  const int64_t d = lg_ptr[i + 1] - base;
-  const unsigned long long hi = hmask[i];
-  for (int64_t p = threadIdx.x; p < d; p += blockDim.x) {
-    const int32_t x = lg_col[base + p];
+  const unsigned long long hi = info[i].heavy;
+  bool dup = false;
+  auto write = [&](int64_t pos, const EdgeInfo& ix, uint32_t m) {
+    const unsigned long long hv = ix.heavy & ~hi;  // heavy nodes of e_x outside e_i
+    const uint32_t p = uint32_t(__popc(m)), o = ix.size - p;
+    if (o == 0 && p == uint32_t(a)) dup = true;
+    rec[pos] = make_uint4(m, o | (o > uint32_t(__popcll(hv)) ? kRecLight : 0u), uint32_t(hv), uint32_t(hv >> 32));
+    recm[pos] = m;
+    rsz[pos] = uint16_t(p | ix.size << 8);
+  };
+  // e_x's nodes against e_i's, four at a time, their loads issued together
+  // before any is used; -1 pads past the list's end
+  auto compare = [&](int64_t x, int64_t pos) {
+    const EdgeInfo ix = info[x];
+    const int64_t q0 = ptr[x], q1 = q0 + ix.size;
     uint32_t m = 0;
-    const int64_t q0 = ptr[x], q1 = ptr[x + 1];
-    const unsigned long long hv = hmask[x] & ~hi;  // heavy nodes of e_x outside e_i
-    // four of e_x's nodes at a time, their loads issued together before any
-    // is used; -1 pads past the list's end
     for (int64_t q = q0; q < q1; q += 4) {
       int32_t v[4];
 #pragma unroll
@@ -314,18 +395,69 @@ __global__ __launch_bounds__(256) void k_records(int64_t E, const int64_t* __res
         if (v[u] < 0 || !((filt[(v[u] >> 5) & 31] >> (v[u] & 31)) & 1u)) hb = 0;
         while (lo < hb) {
           const int mid = (lo + hb) >> 1;
-          if (ei[mid] < v[u]) lo = mid + 1; else hb = mid;
+          if (rn.ei[mid] < v[u]) lo = mid + 1; else hb = mid;
         }
-        if (lo < a && ei[lo] == v[u]) m |= 1u << lo;
+        if (lo < a && rn.ei[lo] == v[u]) m |= 1u << lo;
       }
     }
-    const uint32_t o = uint32_t(q1 - q0) - uint32_t(__popc(m));
-    const uint32_t light = o > uint32_t(__popcll(hv)) ? 1u : 0u;  // an outside node that is not heavy
-    if (o == 0 && __popc(m) == a) atomicOr(flags, kFlagDup);
-    rec[base + p] = make_uint4(m, o | (light ? kRecLight : 0u), uint32_t(hv), uint32_t(hv >> 32));
-    recm[base + p] = m;
-    rsz[base + p] = uint16_t(uint32_t(__popc(m)) | ((uint32_t(__popc(m)) + o) << 8));
+    write(pos, ix, m);
+  };
+  uint32_t found = 0;  // entries before the tile
+  for (int t0 = 0; t0 < nwords; t0 += kRowThreads) {
+    const int w = t0 + tid;
+    uint32_t bits = w < nwords ? bm[w] : 0u;
+    uint32_t incl = uint32_t(__popc(bits));
+    for (int off = 1; off < kWave; off <<= 1) {
+      const uint32_t o = uint32_t(__shfl_up(int(incl), off));
+      if (lane >= off) incl += o;
+    }
+    if (lane == kWave - 1) s_wave[wave] = incl;
+    __syncthreads();
+    uint32_t at = incl - uint32_t(__popc(bits)), total = 0;
+    for (int y = 0; y < kRowThreads / kWave; ++y) {
+      if (y < wave) at += s_wave[y];
+      total += s_wave[y];
+    }
+    if (w == int(il >> 5)) up_first[i] = int32_t(found + at + uint32_t(__popc(bits & ((1u << (il & 31)) - 1u))));
+    for (; bits; bits &= bits - 1u) stage[at++] = uint16_t(tid * 32 + __ffs(bits) - 1);
+    __syncthreads();
+    for (uint32_t r0 = tid; r0 < total; r0 += kRowThreads * kRowUnroll) {
+      int64_t x[kRowUnroll];
+      EdgeInfo ix[kRowUnroll];
+#pragma unroll
+      for (int u = 0; u < kRowUnroll; ++u) {
+        const uint32_t r = min(r0 + u * kRowThreads, total - 1u);
+        x[u] = int64_t(t0) * 32 + stage[r];
+        ix[u] = info[e0 + x[u]];
+      }
+#pragma unroll
+      for (int u = 0; u < kRowUnroll; ++u) {
+        const uint32_t r = r0 + u * kRowThreads;
+        if (r >= total) continue;
+        const int64_t pos = base + found + r;
+        lg_col[pos] = int32_t(e0 + x[u]);
+        if ((light[x[u] >> 5] >> (x[u] & 31)) & 1u) {
+          const uint32_t put = atomicAdd(&s_put, 1u);
+          if (put < uint32_t(kRowQueue)) queue[put] = make_uint2(uint32_t(e0 + x[u]), found + r);
+          else compare(e0 + x[u], pos);
+          continue;
+        }
+        uint32_t m = 0;
+        for (int h = 0; h < nh; ++h) m |= uint32_t((ix[u].heavy >> rn.hbit[h]) & 1ull) << rn.hpos[h];
+        write(pos, ix[u], m);
+      }
+    }
+    found += total;
+    __syncthreads();
+    const uint32_t put = min(s_put, uint32_t(kRowQueue));
+    if (put >= uint32_t(kRowThreads) || (put && t0 + kRowThreads >= nwords)) {
+      for (uint32_t y = tid; y < put; y += kRowThreads) compare(queue[y].x, base + queue[y].y);
+      __syncthreads();
+      if (tid == 0) s_put = 0u;
+      __syncthreads();
+    }
   }
+  if (dup) atomicOr(flags, kFlagDup);
 }
 
 __global__ void k_upper_len(int64_t E, const int64_t* __restrict__ lg_ptr,
@@ -443,8 +575,12 @@ mochy_status project_device(mochy_ctx* ctx, mochy_graph* g) {
   const size_t tmpn = scan_tmp_elems(E + 1);
   int64_t* tmp = nullptr;
   int64_t* cnt = nullptr;
-  auto cleanup = [&]() { device_free(ctx, tmp); device_free(ctx, cnt); };
+  EdgeInfo* info = nullptr;  // and the heavy nodes' bitmaps after it
+  auto cleanup = [&]() { device_free(ctx, tmp); device_free(ctx, cnt); device_free(ctx, info); };
+  auto fail = [&](mochy_status e) { cleanup(); return e; };
   if ((rc = device_alloc(ctx, (void**)&tmp, tmpn * 8)) != MOCHY_OK ||
+      (rc = device_alloc(ctx, (void**)&info, size_t(E) * sizeof(EdgeInfo) + size_t(kHeavyBits) * heavy_words(E) * 8)) !=
+          MOCHY_OK ||
       (rc = device_alloc(ctx, (void**)&cnt, size_t(E + 1) * 8)) != MOCHY_OK) {
     cleanup();
     return rc;
@@ -459,10 +595,14 @@ mochy_status project_device(mochy_ctx* ctx, mochy_graph* g) {
   phase_begin(ctx, kPhDegree);
   MOCHY_HIP(hipMemsetAsync(cnt, 0, size_t(E + 1) * 8, st));
   MOCHY_HIP(hipMemsetAsync(ctx->d_flags + 1, 0, sizeof(int32_t), st));
-  if (E > 0)
-    k_proj_degree<<<unsigned(E), 256, bm_bytes, st>>>(E, g->edge_ptr, g->edge_nodes, g->node_ptr,
-                                                      g->node_edges, g->row_graph, g->geoff, cnt,
+  unsigned long long* hrows = reinterpret_cast<unsigned long long*>(info + E);
+  if (E > 0) {
+    k_edge_heavy<<<blocks(heavy_words(E) * kWave, 256), 256, 0, st>>>(E, g->edge_ptr, g->edge_nodes, g->heavy_bit, info,
+                                                                      hrows);
+    k_proj_degree<<<unsigned(E), 256, bm_bytes, st>>>(E, g->edge_ptr, g->edge_nodes, g->node_ptr, g->node_edges,
+                                                      g->heavy_bit, hrows, g->row_graph, g->geoff, cnt,
                                                       ctx->d_flags + 1);
+  }
   launch_exclusive_scan_i64(cnt, g->lg_ptr, E + 1, tmp, st);
   phase_end(ctx, kPhDegree);
   MOCHY_HIP(hipMemcpyAsync(ctx->h_small, g->lg_ptr + E, 8, hipMemcpyDeviceToHost, st));
@@ -480,19 +620,15 @@ mochy_status project_device(mochy_ctx* ctx, mochy_graph* g) {
   if ((rc = device_alloc(ctx, (void**)&g->rsz, size_t(std::max<int64_t>(twoW, 1)) * 2)) != MOCHY_OK) { cleanup(); return rc; }
   g->bytes += size_t(twoW) * 26;
   phase_begin(ctx, kPhRows);
+  if (2 * bm_bytes > 32 * 1024)
+    MOCHY_HIP_OR(hipFuncSetAttribute((const void*)k_proj_rows, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     int(2 * bm_bytes)), fail);
   if (E > 0)
-    k_proj_fill<<<unsigned(E), 256, bm_bytes, st>>>(E, g->edge_ptr, g->edge_nodes, g->node_ptr,
-                                                    g->node_edges, g->row_graph, g->geoff, g->lg_ptr,
-                                                    g->lg_col, g->up_first);
+    k_proj_rows<<<unsigned(E), kRowThreads, 2 * bm_bytes, st>>>(
+        E, g->edge_ptr, g->edge_nodes, g->node_ptr, g->node_edges, g->heavy_bit, info, hrows, g->row_graph, g->geoff,
+        g->lg_ptr, g->lg_col, g->up_first, g->rec, g->recm, g->rsz, ctx->d_flags);
   phase_end(ctx, kPhRows);
-  // 7. records (cnt, free until the upper-row prefix, holds the heavy masks)
   phase_begin(ctx, kPhRecords);
-  if (E > 0) {
-    unsigned long long* hmask = reinterpret_cast<unsigned long long*>(cnt);
-    k_edge_heavy<<<blocks(E, 256), 256, 0, st>>>(E, g->edge_ptr, g->edge_nodes, g->heavy_bit, hmask);
-    k_records<<<unsigned(E), 256, 0, st>>>(E, g->edge_ptr, g->edge_nodes, hmask, g->lg_ptr, g->lg_col,
-                                           g->rec, g->recm, g->rsz, ctx->d_flags);
-  }
   // upper-row prefix (hyperwedge order for sampling)
   k_upper_len<<<blocks(E + 1, 256), 256, 0, st>>>(E, g->lg_ptr, g->up_first, cnt);
   launch_exclusive_scan_i64(cnt, g->up_ptr, E + 1, tmp, st);
