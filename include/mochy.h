@@ -132,10 +132,9 @@ const char* mochy_last_error(const mochy_ctx* ctx);
                                     8: 32 waves), by the pair kernel that takes a lane per
                                     pair (rows of few neighbour groups, every-pair counting);
                                     no launch has more waves than work items; same counts */
-#define MOCHY_OPT_CACHE_BYTES 9  /* device buffers of 64 MiB or more that a call frees are
-                                    kept by the context, up to this many bytes in all, and
-                                    reused by later calls on it (default half of the
-                                    device memory; 0 = free at once, releasing what is
+#define MOCHY_OPT_CACHE_BYTES 9  /* device buffers that a call frees are kept by the
+                                    context, up to this many bytes in all, and reused
+                                    by later calls on it (default half of the device memory; 0 = free at once, releasing what is
                                     kept); an allocation that fails first releases them
                                     (this context's only: several contexts on one device
                                     should share the memory by their limits);

@@ -279,13 +279,29 @@ void cache_release(mochy_ctx* ctx) {
   ctx->cache_bytes = 0;
 }
 
-// Buffers of at least kCacheMinBytes go through a per-context cache: a freed
-// block is kept (up to cache_limit bytes in all) and handed to a later
-// request that it fits with at most half of it unused.  Freeing and mapping
-// again the hundred-odd GB that a batch of 65 graphs holds costs up to
-// seconds per call; reusing the blocks costs nothing.  A context works on one
+// Buffers go through a per-context cache: a freed block is kept (up to
+// cache_limit bytes in all) and handed to a later request that it fits with at
+// most half of it unused.  Freeing and mapping again the hundred-odd GB that a
+// batch of 65 graphs holds costs up to seconds per call; reusing the blocks
+// costs nothing.  A context works on one
 // stream, so a reused block's earlier readers are ordered before its new
 // writers.
+// Small blocks as well: a call on 4,009 hyperedges takes and gives back 37, and
+// the stream-ordered allocator's calls were 1.36 ms of its 3.69 (hipFreeAsync
+// 23 us, hipMallocAsync 14 us each).  Sizes come in steps of a quarter of a
+// power of two, whole 2 MiB pages from there on, so that calls of about the same
+// size find each other's blocks; the number kept is bounded by what the calls
+// use at once of each step.
+static size_t cache_size(size_t n) {
+  size_t step = size_t(2) << 20;
+  if (n < step) {
+    step = 64;
+    while (step * 8 < n) step <<= 1;  // n in (4, 8] steps
+    if (n <= 256) return 256;
+  }
+  return (n + step - 1) / step * step;
+}
+
 mochy_status device_alloc(mochy_ctx* ctx, void** p, size_t bytes) {
   *p = nullptr;
   size_t n = std::max<size_t>(bytes, 8);
@@ -300,8 +316,9 @@ mochy_status device_alloc(mochy_ctx* ctx, void** p, size_t bytes) {
     ctx->arena_used = at + n;
     return MOCHY_OK;
   }
-  const bool cached = ctx->cache_limit > 0 && n >= kCacheMinBytes;
+  const bool cached = ctx->cache_limit > 0;
   if (cached) {
+    n = cache_size(n);
     auto it = ctx->cache_free.lower_bound(n);
     if (it != ctx->cache_free.end() && it->first / 2 <= n) {
       *p = it->second;
@@ -309,7 +326,6 @@ mochy_status device_alloc(mochy_ctx* ctx, void** p, size_t bytes) {
       ctx->cache_free.erase(it);
       return MOCHY_OK;
     }
-    n = (n + (size_t(2) << 20) - 1) & ~((size_t(2) << 20) - 1);  // whole 2 MiB pages
   }
   hipError_t e = raw_alloc(ctx, p, n);
   if (e != hipSuccess && !ctx->cache_free.empty()) {  // give the cached blocks back and retry

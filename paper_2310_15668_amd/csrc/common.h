@@ -49,7 +49,7 @@ struct mochy_ctx {
   char* arena = nullptr;              // nullptr: ordinary allocation
   size_t arena_cap = 0, arena_used = 0;
   void* noalloc_scratch = nullptr;    // this device's scratch array (from hipGetSymbolAddress)
-  // freed transient buffers of at least kCacheMinBytes kept for reuse on this
+  // freed buffers kept for reuse on this
   // context's stream (MOCHY_OPT_CACHE_BYTES): size -> block, and the size of
   // every block handed out from or destined for the cache
   int64_t cache_limit = 0;            // bytes (half the device memory from creation)
@@ -238,7 +238,6 @@ extern const size_t kNoallocBytes;
 mochy_status device_alloc(mochy_ctx* ctx, void** p, size_t bytes);
 void device_free(mochy_ctx* ctx, void* p);
 void cache_release(mochy_ctx* ctx);  // frees every cached block
-constexpr size_t kCacheMinBytes = size_t(64) << 20;
 
 // Largest graph (hyperedges) whose row bitmap and rank table fit in LDS.
 constexpr int64_t kMaxGraphEdges = 200000;

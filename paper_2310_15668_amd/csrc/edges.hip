@@ -991,13 +991,8 @@ mochy_status edges_device(mochy_ctx* ctx, const mochy_graph* g, int64_t n0, int6
   const size_t fixed = size_t(g->E) * 17 + size_t(nnz) * (kHistW + 1) * 4 + size_t(g->ng) * 4 + 256;
   const size_t per = size_t(t.slots) * sizeof(uint2) + size_t(t.rows) * (4 + sizeof(uint4) + sizeof(GroupInfo)) + 32;
   int64_t batch = std::min(std::min(s, kMaxBatch), std::max<int64_t>(int64_t(kBatchBytes / per), 1));
-  mochy_status rc = MOCHY_ENOMEM;
-  // from kCacheMinBytes on a block is kept for the next call; one of some MB is
-  // made as large, as taking it from the device and giving it back costs a
-  // millisecond and more
-  if (fixed + size_t(batch) * per > kCacheMinBytes / 16 && fixed + size_t(batch) * per < kCacheMinBytes)
-    rc = device_alloc(ctx, (void**)&blob, kCacheMinBytes);
-  while (rc != MOCHY_OK && (rc = device_alloc(ctx, (void**)&blob, fixed + size_t(batch) * per)) != MOCHY_OK) {
+  mochy_status rc;
+  while ((rc = device_alloc(ctx, (void**)&blob, fixed + size_t(batch) * per)) != MOCHY_OK) {
     if (batch == 1) return done(rc);
     batch = (batch + 1) / 2;
   }
