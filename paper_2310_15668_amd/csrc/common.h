@@ -131,6 +131,7 @@ struct mochy_graph {
   int32_t* xnodes = nullptr;             // [xoff[nnz]]: node list of the hyperedge at each slot
   int64_t* deg = nullptr;                // [E]: line-graph degrees
   uint64_t* hmask = nullptr;             // [E]: heavy nodes held by each hyperedge (bit = heavy index)
+  unsigned long long* dense = nullptr;   // [0]: mask of the heavy nodes with dense lists; [2..]: the lists as bitmaps
   // sets of 4 to 6 heavy nodes: open-addressed table (key = set as a mask of
   // heavy indices, 0 = free) of the hyperedges holding the set, by size
   unsigned long long* hbig_key = nullptr;  // [1 << hbig_log2]

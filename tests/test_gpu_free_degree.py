@@ -102,3 +102,40 @@ def test_repeats(ctx, kind):
     with pytest.raises(M.MochyError) as e:
         M.mochy_project(ctx, ptr, nodes, 12 + 4004, LG_FREE)
     assert e.value.status == -2
+
+
+@pytest.mark.parametrize("E", [131071, 131073, 262145, 524289, 1048700])
+def test_selection_tiles(ctx, E):
+    """Rows drawn from one tile of all hyperedges, at the sizes where the tile
+    and its block grow, and from several tiles."""
+    import paper_2310_15668_amd as M
+    rng = np.random.default_rng(E)
+    top = np.minimum((rng.pareto(0.5, size=E) * 3).astype(np.int64), 1999)  # a few nodes in many hyperedges
+    own = 2000 + np.arange(E)
+    nodes = np.stack([top, own], axis=1).astype(np.int32).reshape(-1)
+    ptr = np.arange(E + 1, dtype=np.int64) * 2
+    print(f"[gpu] selection |E|={E}", flush=True)
+    g = M.mochy_project(ctx, ptr, nodes, 2000 + E, LG_FREE)
+    try:
+        held = np.bincount(top)
+        pairs = held * (held - 1) // 2
+        assert g.num_hyperwedges == pairs.sum()
+        # each sample {i, j} of a node in n hyperedges meets the n - 2 others, all in one class
+        raw431 = np.asarray(M.mochy_count_sampled(ctx, g, 4000, 7)[2])
+        assert (raw431 > 0).sum() == 1
+        order = np.argsort(top, kind="stable")
+        first = np.concatenate([[0], np.cumsum(held)])
+        place = np.empty(E, dtype=np.int64)
+        place[order] = np.arange(E) - first[top[order]]
+        up = held[top] - 1 - place  # neighbours above each row
+        ends = np.cumsum(up)
+        want = sum(int(held[top[int(np.searchsorted(ends, w, side="right"))]]) - 2
+                   for w in (sample_wedge(n, 7, int(pairs.sum())) for n in range(4000)))
+        assert raw431.sum() == want
+    finally:
+        g.close()
+
+
+def sample_wedge(n, seed, W):
+    x = native.philox4x32_10([n & 0xffffffff, n >> 32, 0, 0], [seed & 0xffffffff, seed >> 32])
+    return ((x[1] << 32 | x[0]) * W) >> 64
