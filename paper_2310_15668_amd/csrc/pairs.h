@@ -339,8 +339,14 @@ __device__ __forceinline__ void wave_prefix(uint32_t* bins, int n, uint32_t star
 // kMfmaCols columns of a row; rows of fewer than kMfmaRowGroups groups, and
 // rows whose centre holds more than kMfmaMaxEdge nodes (two mask bits carry a
 // window slot), stay with the lane-per-pair kernel.
+// The line at 128 groups, one work item's columns: 9 graphs of 3,001 hyperedges
+// (rows of 300 groups on average) 1.80 ms for their pairs, 2.46 with the line at
+// 512, 1.93 at 256, 1.79 at 64.  A graph without a row of kMfmaMinDegree
+// neighbours stays with the lane-per-pair kernel altogether: the two launches
+// and the sorting cost more than they give (500 hyperedges: 0.06 ms, 0.12 with).
 constexpr int kMfmaCols = 128;
-constexpr int kMfmaRowGroups = 512;
+constexpr int kMfmaRowGroups = 128;
+constexpr int kMfmaMinDegree = 512;
 constexpr int kMfmaMaxEdge = 30;
 constexpr int kGroupSlack = 128;  // groups readable past the end of the group arrays
 
