@@ -270,13 +270,18 @@ static void raw_free(mochy_ctx* ctx, void* p) {
   else (void)hipFree(p);
 }
 
-void cache_release(mochy_ctx* ctx) {
+static void release_cached(mochy_ctx* ctx) {  // with cache_mu held
   for (auto& kv : ctx->cache_free) {
     ctx->cache_live.erase(kv.second);
     raw_free(ctx, kv.second);
   }
   ctx->cache_free.clear();
   ctx->cache_bytes = 0;
+}
+
+void cache_release(mochy_ctx* ctx) {
+  std::lock_guard<std::mutex> lock(ctx->cache_mu);
+  release_cached(ctx);
 }
 
 // Buffers go through a per-context cache: a freed block is kept (up to
@@ -316,6 +321,9 @@ mochy_status device_alloc(mochy_ctx* ctx, void** p, size_t bytes) {
     ctx->arena_used = at + n;
     return MOCHY_OK;
   }
+  // a graph may be freed by another thread than the one that runs a call on its
+  // context (a caller's garbage collector)
+  std::lock_guard<std::mutex> lock(ctx->cache_mu);
   const bool cached = ctx->cache_limit > 0;
   if (cached) {
     n = cache_size(n);
@@ -330,7 +338,7 @@ mochy_status device_alloc(mochy_ctx* ctx, void** p, size_t bytes) {
   hipError_t e = raw_alloc(ctx, p, n);
   if (e != hipSuccess && !ctx->cache_free.empty()) {  // give the cached blocks back and retry
     (void)hipGetLastError();
-    cache_release(ctx);
+    release_cached(ctx);
     (void)hipStreamSynchronize(ctx->stream);
     e = raw_alloc(ctx, p, n);
   }
@@ -345,7 +353,10 @@ mochy_status device_alloc(mochy_ctx* ctx, void** p, size_t bytes) {
 }
 
 void device_free(mochy_ctx* ctx, void* p) {
-  if (!p || ctx->arena) return;  // arena blocks are released with the call
+  if (!p) return;
+  const char* const arena = static_cast<const char*>(ctx->noalloc_scratch);
+  if (arena && p >= arena && p < arena + kNoallocBytes) return;  // released with its call
+  std::lock_guard<std::mutex> lock(ctx->cache_mu);
   auto it = ctx->cache_live.find(p);
   if (it != ctx->cache_live.end() && ctx->cache_bytes + int64_t(it->second) <= ctx->cache_limit) {
     ctx->cache_free.emplace(it->second, p);  // stays in cache_live until released

@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <map>
+#include <mutex>
 #include <string>
 #include <unordered_map>
 #include <vector>
@@ -54,6 +55,7 @@ struct mochy_ctx {
   // every block handed out from or destined for the cache
   int64_t cache_limit = 0;            // bytes (half the device memory from creation)
   int64_t cache_bytes = 0;
+  std::mutex cache_mu;                // guards the cache
   std::multimap<size_t, void*> cache_free;
   std::unordered_map<void*, size_t> cache_live;
   int num_cus = 0;
