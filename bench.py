@@ -18,10 +18,10 @@ light-node correction, and the 457 counts back on the host.
 
 Prints one JSON line.  value = connected triples classified per second
 (sum of all h-motif counts / step time).  The roofline object is for the pair
-kernel (integer-ALU bound: algorithmic operations per pair of neighbour
-groups against the integer VALU rate measured in the same run), timed with
-HIP events on the stream it runs on; correction_roofline is the light-pair
-fix kernel's (bytes against HBM).  The same line carries the batched CP
+kernels (pairs of neighbour groups against the rate at which the LDS takes
+their adds, and the vector and matrix units the pairs that count only when
+open), timed with HIP events on the stream they run on; correction_roofline is
+the light-pair kernel's (bytes against HBM).  The same line carries the batched CP
 comparison (base + 64 copies at --scale, one call against 65 sequential
 calls, identical counts) and a serving stream (--requests at --rate through
 the continuous-batching server, p50/p99 latency), and the CPU baseline: the
@@ -38,10 +38,10 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-PAIR_KERNEL_SRC = os.path.join(ROOT, "paper_2310_15668_amd", "csrc", "exact.hip")
-COUNTERS_SUMMARY = os.path.join(ROOT, "profiles", "k_exact_grouped_medium_counters.md")
+PAIR_KERNEL_SRC = os.path.join(ROOT, "paper_2310_15668_amd", "csrc", "pairs.hip")
+COUNTERS_SUMMARY = os.path.join(ROOT, "profiles", "k_pairs_medium_counters.md")
 FIX_KERNEL_SRC = os.path.join(ROOT, "paper_2310_15668_amd", "csrc", "correct.hip")
-FIX_SUMMARY = os.path.join(ROOT, "profiles", "k_light_fix_medium_counters.md")
+FIX_SUMMARY = os.path.join(ROOT, "profiles", "k_light_dense_medium_counters.md")
 # the on-the-fly enumeration phase: k_enum (free.hip), k_memo and k_msample
 # (memo.hip), their shared walk (walk.h)
 ENUM_SRCS = [os.path.join(ROOT, "paper_2310_15668_amd", "csrc", f) for f in ("free.hip", "memo.hip", "walk.h")]
@@ -82,45 +82,26 @@ def summary_values(summary, source):
 
 # Integer vector-ALU ceiling from the chip's unit counts: 256 CUs, each with
 # 4 SIMD units of 16 lanes (one wave64 instruction per CU per cycle), at the
-# 2.4 GHz peak engine clock: 39.3e12 32-bit lane instructions per second.  A
-# pure integer-VALU kernel of the pair kernel's instruction mix
-# (mochy_calibrate_valu) sustains about that on the box, so the roofline
-# takes the measured rate, from the same run, as its peak.
+# 2.4 GHz peak engine clock: 39.3e12 32-bit lane instructions per second
+# (mochy_calibrate_valu sustains about that; it is run beside every step).
 NUM_CUS, CLOCK_HZ, LANES = 256, 2.4e9, 64
 VALU_PEAK_DERIVED = NUM_CUS * LANES * CLOCK_HZ
 
-# Algorithmic integer vector instructions per unit of the exact pair kernel
-# (Lemma 2's region sizes from the two neighbours' records; counted as
-# instructions, as the calibrated ceiling is, so a packed instruction that
-# does two 16-bit operations counts once; the class-table read and the
-# histogram add are LDS operations and not counted):
-#  * a pair of neighbour groups that both have a member above the centre
-#    (its class is needed in full): the three mask intersections (centre
-#    nodes, two words of heavy outside nodes), three population counts with
-#    their offsets added in the same instruction (t + 2, and R5 + 2 in two),
-#    a shift-or packing t + 2 and R5 + 2 into the halves of one word, a
-#    compare of that word for the disjointness test (t = R5 = 0), a
-#    shift-add for 2 (|e_i| - |e_i ∩ e_k| + t), the seven ternary digits
-#    max(2 - R, 0) as one saturating subtract and three packed ones (two
-#    digits each), the base-3 code doubled into the table's byte offset as
-#    three two-term dot products, the weight N_j N_k or A_j A_k as a select
-#    of the lane's (0, N_k) or (A_k, 0) and a two-term dot product with j's
-#    counts packed as 16-bit halves, and one add for the histogram address:
-#    19 (21 where a row reaches 2^16 neighbours, the counts no longer fit 16
-#    bits and the weight takes two selects and two multiplies for 48 bits);
-#  * any other pair of groups (counted only when open): the centre-node
-#    intersection, two AND-ORs for the heavy words, max(1 - x, 0) and a
-#    multiply-add into the run's sum over disjoint groups: 5.
-OPS_FULL_PAIR, OPS_OPEN_PAIR = 19, 5
-WIDE_ROW = 1 << 16  # line-graph degree from which a pair weight takes 48 bits
-# Algorithmic bytes of the light-pair fix kernel: the partner row's entry
-# (4-byte hyperedge id) for every scanned entry, and for every centre it finds
-# the partner row's 4-byte record mask and owner row's 2-byte size word.
-FIX_BYTES_SCANNED, FIX_BYTES_CENTRE = 4, 6
+# What the pair kernels cannot do without, in CU cycles per 64 pairs (a wave):
+#  * a pair of neighbour groups that both have a member above the centre: one
+#    LDS add of j's counts to a counter of k's, 4.1 cycles with every lane at a
+#    word of its own;
+#  * any other pair (counted only when open): two half-rate vector instructions
+#    for two rows, 1.1 cycles, beside 0.75 of MFMA.
+FULL_PAIR_CYCLES, OPEN_PAIR_CYCLES = 4.1, 1.85
+# Algorithmic bytes of the light-pair kernel: the overlap table's byte of every
+# scanned entry, and for every centre it finds a 4-byte record mask and a
+# 2-byte size word.
+FIX_BYTES_SCANNED, FIX_BYTES_CENTRE = 1, 6
 
 
 def valu_issue(kernel_ms, ceiling):
-    """The pair kernel's VALU wave-instructions per launch (SQ_INSTS_VALU from
+    """The pair kernels' VALU wave-instructions per step (SQ_INSTS_VALU from
     the committed counter summary) over this run's kernel time, per CU per
     cycle, beside the calibrated ceiling in the same unit; None if the
     counters are stale."""
@@ -132,7 +113,7 @@ def valu_issue(kernel_ms, ceiling):
     peak = ceiling / (LANES * NUM_CUS * CLOCK_HZ)
     return {"valu_wave_instructions_per_launch": n, "per_cu_per_cycle": rate,
             "calibrated_per_cu_per_cycle": peak, "frac": rate / peak,
-            "source": "profiles/k_exact_grouped_medium_counters.md"}
+            "source": "profiles/k_pairs_medium_counters.md"}
 
 
 def valu_calibration(M, ctx, iters=1 << 16, runs=3):
@@ -758,9 +739,10 @@ def medium_exact(args):
     identity_ok = (s_open + 3 * s_closed) == st["candidates"]
 
     pair_ms = phase_sum["exact_pairs"] / K
-    ops_full = OPS_FULL_PAIR + (2 if st["max_line_degree"] >= WIDE_ROW else 0)
-    ops = ops_full * xs["group_pairs_full"] + OPS_OPEN_PAIR * xs["group_pairs_open"]
-    achieved = ops / (pair_ms * 1e-3)
+    pairs = xs["group_pairs_full"] + xs["group_pairs_open"]
+    achieved = pairs / (pair_ms * 1e-3)
+    cycles = FULL_PAIR_CYCLES * xs["group_pairs_full"] + OPEN_PAIR_CYCLES * xs["group_pairs_open"]
+    peak = pairs / (cycles / LANES / (NUM_CUS * CLOCK_HZ))
     fix_ms = phase_sum["exact_fix_kernel"] / K
     fix_bytes = FIX_BYTES_SCANNED * xs["fix_scanned"] + FIX_BYTES_CENTRE * xs["fix_centres"]
     out = {
@@ -775,25 +757,23 @@ def medium_exact(args):
                    "incidences": st["nnz"], "hyperwedges": st["hyperwedges"],
                    "max_line_degree": st["max_line_degree"], "candidates": st["candidates"],
                    "connected_triples": triples, "parallelism": "single GPU"},
-        "roofline": {"bound": "alu", "kernel": "k_exact_grouped (MoCHy-E pairs of neighbour groups)",
-                     "achieved": achieved / 1e12, "peak": valu_peak / 1e12, "unit": "TOP/s",
-                     "frac": achieved / valu_peak, "traffic": measured_traffic(),
-                     "model": f"{ops_full} integer vector lane instructions per pair of neighbour groups "
-                              f"classified in full, {OPS_OPEN_PAIR} per other pair (counted only when open)",
-                     "peak_source": "integer VALU rate of mochy_calibrate_valu measured in this run "
-                                    f"(chip-derived: 256 CUs x 64 lanes x 2.4 GHz = "
-                                    f"{VALU_PEAK_DERIVED / 1e12:.1f} TOP/s)",
-                     "peak_derived": VALU_PEAK_DERIVED / 1e12,
+        "roofline": {"bound": "lds", "kernel": "k_pairs_full, k_pairs_open, k_exact_grouped "
+                                               "(MoCHy-E pairs of neighbour groups)",
+                     "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "Tpairs/s",
+                     "frac": achieved / peak, "traffic": measured_traffic(),
+                     "model": f"{FULL_PAIR_CYCLES} CU cycles per 64 pairs of neighbour groups counted in full (an LDS "
+                              f"add), {OPEN_PAIR_CYCLES} per 64 others (vector and matrix issue)",
+                     "peak_source": "cycle costs measured alone, 256 CUs at 2.4 GHz",
                      "kernel_ms": pair_ms, "group_pairs_full": xs["group_pairs_full"],
                      "group_pairs_open": xs["group_pairs_open"],
                      "candidates_per_s": st["candidates"] / (pair_ms * 1e-3),
                      "valu_issue": valu_issue(pair_ms, valu_peak)},
-        "correction_roofline": {"bound": "hbm", "kernel": "k_light_fix (light-pair correction)",
+        "correction_roofline": {"bound": "hbm", "kernel": "k_light_dense (light-pair correction)",
                                 "achieved": fix_bytes / (fix_ms * 1e-3) / 1e9 if fix_ms else None,
                                 "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                 "frac": fix_bytes / (fix_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if fix_ms else None,
                                 "traffic": measured_traffic(FIX_SUMMARY, FIX_KERNEL_SRC),
-                                "model": f"{FIX_BYTES_SCANNED} B per scanned row entry + {FIX_BYTES_CENTRE} B "
+                                "model": f"{FIX_BYTES_SCANNED} B per scanned entry + {FIX_BYTES_CENTRE} B "
                                          "per centre examined",
                                 "kernel_ms": fix_ms, "scanned_entries": xs["fix_scanned"],
                                 "centres": xs["fix_centres"], "light_pairs": xs["light_pairs"]},

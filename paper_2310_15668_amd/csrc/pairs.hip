@@ -23,8 +23,8 @@
 // Measured on the medium workload (85,476 hyperedges; 4.4e11 pairs of groups
 // above the centre, 7.7e11 others): 77 ms and 71 ms, where classifying pair by
 // pair (19 and 5 vector instructions) took 345 ms for both.  k_pairs_full is
-// bound by LDS atomics: a ds_add_u32 of 64 lanes takes 4.1 cycles of a CU
-// whatever its addresses, 46 ms of the 77 in all, the rest being counters read
+// bound by LDS atomics: a ds_add_u32 of 64 lanes at words of their own takes 4.1
+// cycles of a CU, 46 ms of the 77 in all, the rest being counters read
 // back, rows without a full block and latency at two waves per SIMD.
 // k_pairs_open spends two half-rate vector instructions on two rows x 64
 // columns, beside 0.75 cycles of MFMA per 64 pairs: a bound of 35 ms.
