@@ -48,10 +48,16 @@
 
 namespace {
 
-constexpr int kCopies = 2;                 // histogram copies per wave (picked by lane)
-constexpr int kStride = kHistSlots + 1;    // odd stride spreads the copies over banks
-constexpr int kWavesPerGroup = 4;
-constexpr int64_t kFlushVisits = int64_t(1) << 26;  // 32 lanes share a copy: counters < 2^32
+// The every-pair kernel's counters, shared by a block's waves: kCopies of each
+// motif's in neighbouring banks, picked by lane, so that no more than 4 lanes
+// of a wave add at one address and take turns (2 copies to a wave: 3.2 ms on
+// 6,029 hyperedges, 4: 2.7, 16 to a block: 2.2).
+constexpr int kCopies = 16;
+constexpr int kMainThreads = 512, kMainWaves = kMainThreads / kWave;
+// visits after which a wave empties the counters: they hold at most as many of
+// each wave, 4 lanes' adds a visit
+constexpr int64_t kFlushVisits = int64_t(1) << 26;
+static_assert(kFlushVisits * kMainWaves * (kWave / kCopies) < (int64_t(1) << 32), "32-bit counters");
 
 // ---------------------------------------------------------------------------
 // Scheduling (the lists pairs.h describes): one block per graph sorts its rows
@@ -197,83 +203,85 @@ __global__ __launch_bounds__(1024) void k_schedule(int64_t c0, int64_t c1, const
   }
 }
 
-// Walk j over [j0, j1) against the lane's k.  kCountAll: both j and k are
-// above the centre (count every pair); otherwise count only disjoint pairs.
-// kDiag: the j range overlaps the lane block, so require j < kp.
-template <bool kCountAll, bool kDiag>
-__device__ __forceinline__ void pair_step(const uint4& rj, int j, uint32_t a, const Side& k,
-                                          uint32_t khl, uint32_t khh, int kp, bool valid,
-                                          const uint16_t* __restrict__ lut, uint32_t* hist) {
-  const uint32_t mj = rj.x;
-  bool act = valid;
-  if (kDiag) act = act && (j < kp);
-  if (!kCountAll) {
-    // below the centre only disjoint pairs count: test with ANDs, no popcounts
-    act = act && (((mj & k.m) | (rj.z & khl) | (rj.w & khh)) == 0u);
-  }
-  if (act) {
-    const uint32_t t = kCountAll ? uint32_t(__popc(mj & k.m)) : 0u;
-    const uint32_t r5 = kCountAll ? uint32_t(__popc(rj.z & khl) + __popc(rj.w & khh)) : 0u;
-    const uint32_t code = pair_code(a, __popc(mj), rj.y & 0xffu, k, t, r5);
-    atomicAdd(&hist[lut[code]], 1u);
-  }
-}
+// The lane's k as the walks take it.
+struct LaneSide {
+  uint32_t m, hl, hh, kso;  // masks; |e_i ∩ e_k| | outside count << 16
+  uint32_t aks2;            // 2 (|e_i| - |e_i ∩ e_k|) - 4
+  uint32_t aksd;            // 2 (|e_i| - |e_i ∩ e_k|)
+  uint32_t open;            // its digits R6 and R3 of a disjoint pair, and those of t = R5 = 0
+  uint32_t one;             // 1, 0 past the row's end
+  int kp;
+};
 
-// Walk j over [j0, j1) against the lane's k, four records per step (the
-// four uniform loads are issued together).  kCountAll: both j and k are
-// above the centre (count every pair); otherwise count only disjoint pairs.
-// kDiag: the j range overlaps the lane block, so require j < kp.
-template <bool kCountAll, bool kDiag>
-__device__ __forceinline__ void walk(const uint4* __restrict__ row, int j0, int j1, uint32_t a,
-                                     const Side& k, int kp, bool valid,
-                                     const uint16_t* __restrict__ lut, uint32_t* hist) {
-  const uint32_t khl = uint32_t(k.h), khh = uint32_t(k.h >> 32);
-  int j = j0;
-  for (; j + 4 <= j1; j += 4) {
-    const uint4 r0 = row[j], r1 = row[j + 1], r2 = row[j + 2], r3 = row[j + 3];
-    pair_step<kCountAll, kDiag>(r0, j, a, k, khl, khh, kp, valid, lut, hist);
-    pair_step<kCountAll, kDiag>(r1, j + 1, a, k, khl, khh, kp, valid, lut, hist);
-    pair_step<kCountAll, kDiag>(r2, j + 2, a, k, khl, khh, kp, valid, lut, hist);
-    pair_step<kCountAll, kDiag>(r3, j + 3, a, k, khl, khh, kp, valid, lut, hist);
-  }
-  for (; j < j1; ++j) pair_step<kCountAll, kDiag>(row[j], j, a, k, khl, khh, kp, valid, lut, hist);
-}
-
-// Adds a wave's histogram copies into graph g's global counts and clears them.
-__device__ __forceinline__ void flush_wave(uint32_t* whist, int lane, int64_t g,
-                                           unsigned long long* hist_out) {
-  __builtin_amdgcn_wave_barrier();
-  for (int t = lane; t < kHistSlots; t += kWave) {
-    unsigned long long s = 0;
-    for (int c = 0; c < kCopies; ++c) {
-      s += whist[c * kStride + t];
-      whist[c * kStride + t] = 0u;
+// Pairs of the lane's k and kN records from j on (uniform); the class table
+// reads are issued together.  kCountAll: both j and k are above the centre (every pair counts);
+// otherwise only disjoint pairs count, whose codes are k's digits, j's (scalar
+// work) and R1.  kDiag: the j range overlaps the lane block, so require j < kp.
+template <int kN, bool kCountAll, bool kDiag>
+__device__ __forceinline__ void pair_steps(const uint4* __restrict__ row, int j, const LaneSide& k,
+                                           const uint16_t* __restrict__ lut, char* hist) {
+  uint32_t code[kN], w[kN];
+#pragma unroll
+  for (int u = 0; u < kN; ++u) {
+    const uint4 rj = row[j + u];
+    const uint32_t pj = uint32_t(__popc(rj.x)), oj = rj.y & 0xffu;
+    w[u] = kDiag && j + u >= k.kp ? 0u : k.one;
+    if (kCountAll) {
+      uint32_t t2, tr;
+      pair_counts(rj.x & k.m, rj.z & k.hl, rj.w & k.hh, t2, tr);
+      code[u] = pair_rcode2(t2, tr, k.aks2, pj | (2u * pj + 4u) << 8 | oj << 16, k.kso);
+    } else {
+      const uint32_t x = and_or(rj.w, k.hh, and_or(rj.z, k.hl, rj.x & k.m));
+      // R1 held in range for a pair that overlaps
+      code[u] = min(usat(2u * pj + 4u, k.aksd), 4u) + k.open + (54u * usat(2u, pj) + 6u * usat(2u, oj));
+      w[u] = x ? 0u : w[u];
     }
-    if (s) atomicAdd(&hist_out[g * kHistSlots + t], s);
   }
-  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int u = 0; u < kN; ++u) code[u] = lut_at(lut, code[u]);
+#pragma unroll
+  for (int u = 0; u < kN; ++u)
+    if (w[u]) atomicAdd(reinterpret_cast<uint32_t*>(hist + code[u]), 1u);
 }
 
-__global__ __launch_bounds__(256) void k_exact_main(
+template <bool kCountAll, bool kDiag>
+__device__ __forceinline__ void walk(const uint4* __restrict__ row, int j0, int j1, const LaneSide& k,
+                                     const uint16_t* __restrict__ lut, char* hist) {
+  int j = j0;
+  for (; j + 8 <= j1; j += 8) pair_steps<8, kCountAll, kDiag>(row, j, k, lut, hist);
+  for (; j < j1; ++j) pair_steps<1, kCountAll, kDiag>(row, j, k, lut, hist);
+}
+
+// Adds the counters at x = first, first + step, .. to graph g's counts and
+// empties them, while other waves may add.
+__device__ __forceinline__ void flush_main(uint32_t (*hist)[kCopies], int first, int step, int64_t g,
+                                           unsigned long long* hist_out) {
+  for (int t = first; t < kHistSlots; t += step) {
+    unsigned long long n = 0;
+    for (int c = 0; c < kCopies; ++c) n += atomicExch(&hist[t][(c + t) % kCopies], 0u);
+    if (n) atomicAdd(&hist_out[g * kHistSlots + t], n);
+  }
+}
+
+__global__ __launch_bounds__(kMainThreads) void k_exact_main(
     const int64_t* __restrict__ edge_ptr, const int64_t* __restrict__ lg_ptr,
     const int32_t* __restrict__ up_first, const uint4* __restrict__ rec, WorkItems I,
     const uint16_t* __restrict__ code_to_id3, unsigned long long* hist_out) {
   __shared__ uint16_t lut[kNumCodes];
-  __shared__ uint32_t hist[kWavesPerGroup * kCopies * kStride];
-  for (int t = threadIdx.x; t < kNumCodes; t += blockDim.x) lut[t] = code_to_id3[t];
-  for (int t = threadIdx.x; t < kWavesPerGroup * kCopies * kStride; t += blockDim.x) hist[t] = 0u;
+  __shared__ uint32_t hist[kHistSlots][kCopies];
+  // by reversed code: byte offsets of the ids' counters
+  for (int t = threadIdx.x; t < kNumCodes; t += blockDim.x) lut[t] = uint16_t(code_to_id3[kNumCodes - 1 - t] * (kCopies * 4u));
+  for (int t = threadIdx.x; t < kHistSlots * kCopies; t += blockDim.x) hist[0][t] = 0u;
   __syncthreads();
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  uint32_t* whist = hist + wave * (kCopies * kStride);
-  uint32_t* myhist = whist + (lane & (kCopies - 1)) * kStride;
+  char* myhist = reinterpret_cast<char*>(&hist[0][lane % kCopies]);
   visit_graphs(I, [&](int g, const ItemRange& items) {
     int64_t visits = 0;
     int32_t i;
     int b;
     while (next_item(items, lane, i, b)) {
       if (visits > kFlushVisits) {
-        flush_wave(whist, lane, g, hist_out);
+        flush_main(hist, lane, kWave, g, hist_out);
         visits = 0;
       }
       const int64_t base = lg_ptr[i];
@@ -283,27 +291,32 @@ __global__ __launch_bounds__(256) void k_exact_main(
       const uint4* __restrict__ row = rec + base;
       const int kp = b * kWave + lane;
       const bool valid = kp < d;
-      Side k;
+      LaneSide k;
       {
         const uint4 rk = valid ? row[kp] : make_uint4(0, 0, 0, 0);
+        const uint32_t ks = uint32_t(__popc(rk.x)), ko = rk.y & 0xffu;
         k.m = rk.x;
-        k.o = rk.y & 0xffu;
-        k.s = __popc(rk.x);
-        k.h = (unsigned long long)rk.z | ((unsigned long long)rk.w << 32);
+        k.hl = rk.z;
+        k.hh = rk.w;
+        k.kso = ks | ko << 16;
+        k.aksd = 2u * (a - ks);
+        k.aks2 = k.aksd - 4u;
+        k.open = 2u * 1458u + 2u * 162u + 486u * usat(2u, ks) + 18u * usat(2u, ko);
+        k.one = valid ? 1u : 0u;
+        k.kp = kp;
       }
       const int blo = b * kWave;
       const int kmax = min(blo + kWave, d);
       visits += int64_t(kmax);
       // j below the centre: count disjoint pairs only
       const int ua = min(u, blo);
-      walk<false, false>(row, 0, ua, a, k, kp, valid, lut, myhist);
-      walk<false, true>(row, max(ua, blo), min(u, kmax), a, k, kp, valid, lut, myhist);
+      walk<false, false>(row, 0, ua, k, lut, myhist);
+      walk<false, true>(row, max(ua, blo), min(u, kmax), k, lut, myhist);
       // j (and so k) above the centre: count every pair
-      walk<true, false>(row, u, blo, a, k, kp, valid, lut, myhist);
-      walk<true, true>(row, max(u, blo), kmax, a, k, kp, valid, lut, myhist);
+      walk<true, false>(row, u, blo, k, lut, myhist);
+      walk<true, true>(row, max(u, blo), kmax, k, lut, myhist);
     }
-    flush_wave(whist, lane, g, hist_out);
-  }, [](int) {});
+  }, [&](int g) { flush_main(hist, threadIdx.x, kMainThreads, g, hist_out); });
 }
 
 // ---------------------------------------------------------------------------
@@ -992,7 +1005,8 @@ mochy_status exact_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, int6
   for (int a = 0; a < ng; a += step) {
     const int b = std::min(ng, a + step);
     if (!grouped) {
-      k_exact_main<<<at_most(lane_grid, entries / kWave + g->E, 4), 256, 0, st>>>(
+      k_exact_main<<<at_most(std::max(1u, lane_grid * 256u / unsigned(kMainThreads)), entries / kWave + g->E, kMainWaves),
+                     kMainThreads, 0, st>>>(
           g->edge_ptr, g->lg_ptr, g->up_first, g->rec, S.items(kItemsLane, a, b), ctx->d_code_to_id3, h);
       continue;
     }
