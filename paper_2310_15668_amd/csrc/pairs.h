@@ -38,19 +38,13 @@ __device__ __forceinline__ uint32_t pk_usat_vs(uint32_t a, uint32_t b) {  // b u
   return r;
 }
 
-// lo(d) * lo(w) + hi(d) * hi(w) + c, 16-bit halves (w uniform): two
-// multiply-adds of a Horner chain in one instruction.
-__device__ __forceinline__ uint32_t dot2(uint32_t d, uint32_t w, uint32_t c) {
-  uint32_t r;
-  asm("v_dot2_u32_u16 %0, %1, %2, %3" : "=v"(r) : "v"(d), "s"(w), "v"(c));
-  return r;
-}
-
-// lo(a) * lo(b) + hi(a) * hi(b), 16-bit halves, both per lane.
-__device__ __forceinline__ uint32_t dot2_vv(uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_dot2_u32_u16 %0, %1, %2, 0" : "=v"(r) : "v"(a), "v"(b));
-  return r;
+// lo(a) * lo(b) + hi(a) * hi(b) + c, 16-bit halves: two multiply-adds of a
+// Horner chain in one instruction.  The builtin, not asm: another instruction may
+// read a dot product's result only three wait states later, which the compiler
+// adds where it sees one.
+__device__ __forceinline__ uint32_t dot2(uint32_t a, uint32_t b, uint32_t c) {
+  using u16x2 = uint16_t __attribute__((ext_vector_type(2)));
+  return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b), c, false);
 }
 
 // Twice the reversed ternary code 2186 - code of a pair (code as
@@ -162,7 +156,7 @@ __device__ __forceinline__ void pair_full(const uint4& rj, const typename GroupC
   const bool disjoint = tr == 0x00020002u;  // t = r5 = 0
   rc2 = pair_rcode2(t2, tr, aks2, rj.y, kso);
   if constexpr (kNarrow) {
-    w = dot2_vv(cj, disjoint ? kn16 : ka);
+    w = dot2(cj, disjoint ? kn16 : ka, 0u);
   } else {
     const uint32_t y = disjoint ? kn : ka;
     const uint32_t x = (disjoint ? cj.x : cj.y) & 0xffffffu;
