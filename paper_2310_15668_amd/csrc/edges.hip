@@ -360,8 +360,6 @@ __device__ __forceinline__ void flush(unsigned long long* plus, unsigned long lo
   }
 }
 
-using u16x2 = uint16_t __attribute__((ext_vector_type(2)));
-
 // Both halves held to 2
 __device__ __forceinline__ uint32_t held2(uint32_t x) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, x), u16x2{2, 2}));
@@ -397,8 +395,8 @@ __device__ __forceinline__ void group_pairs(const uint4* __restrict__ grec, cons
     // q + 4 twice over; 2 + q less each side's outside count and the other's size
     const uint32_t q4 = dot2(tr, 0x00010001u, 0u);
     const uint32_t qq = q4 | q4 << 16;
-    const uint32_t dj = held2(pk_usat_vs(qq, fj.far));  // (R2 of the path through j, R3 of the path through k)
-    const uint32_t dk = held2(pk_usat_vv(qq, far_k));   // (R3 through j, R2 through k)
+    const uint32_t dj = held2(pk_usat(qq, fj.far));  // (R2 of the path through j, R3 of the path through k)
+    const uint32_t dk = held2(pk_usat(qq, far_k));   // (R3 through j, R2 through k)
     const uint32_t r5 = q4 == 5u ? 162u : 0u;
     cj[u] = dot2(dk, 18u, dot2(dj, 6u, r5 + fj.base));
     ck[u] = dot2(dk, 6u << 16, dot2(dj, 18u << 16, r5 + fk.base));

@@ -22,20 +22,10 @@ __device__ __forceinline__ uint32_t cnt_above(uint32_t c) { return c & 0xffffu; 
 __device__ __forceinline__ uint32_t usat(uint32_t a, uint32_t b) { return a > b ? a - b : 0u; }
 
 // max(a - b, 0) on both 16-bit halves at once (a packed saturating subtract).
-__device__ __forceinline__ uint32_t pk_usat_sv(uint32_t a, uint32_t b) {  // a uniform
-  uint32_t r;
-  asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(r) : "s"(a), "v"(b));
-  return r;
-}
-__device__ __forceinline__ uint32_t pk_usat_vv(uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-__device__ __forceinline__ uint32_t pk_usat_vs(uint32_t a, uint32_t b) {  // b uniform
-  uint32_t r;
-  asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(r) : "v"(a), "s"(b));
-  return r;
+using u16x2 = uint16_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_usat(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(
+      uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
 
 // lo(a) * lo(b) + hi(a) * hi(b) + c, 16-bit halves: two multiply-adds of a
@@ -43,7 +33,6 @@ __device__ __forceinline__ uint32_t pk_usat_vs(uint32_t a, uint32_t b) {  // b u
 // read a dot product's result only three wait states later, which the compiler
 // adds where it sees one.
 __device__ __forceinline__ uint32_t dot2(uint32_t a, uint32_t b, uint32_t c) {
-  using u16x2 = uint16_t __attribute__((ext_vector_type(2)));
   return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b), c, false);
 }
 
@@ -65,9 +54,9 @@ __device__ __forceinline__ uint32_t pair_rcode2(uint32_t t2, uint32_t tr, uint32
   const uint32_t pjo = jy & 0x00ff00ffu, pj24 = (jy >> 8) & 0xffu;
   uint32_t v2;  // 2 (aks + t) = 2 t2 + aks2, one shift-add
   asm("v_lshl_add_u32 %0, %1, 1, %2" : "=v"(v2) : "v"(t2), "v"(aks2));
-  const uint32_t d75 = pk_usat_sv(0x00040004u, tr);     // (R7, R5)
-  const uint32_t d63 = pk_usat_vv(tr, kso);             // (R6, R3)
-  const uint32_t d42 = pk_usat_vs(tr, pjo);             // (R4, R2)
+  const uint32_t d75 = pk_usat(0x00040004u, tr);     // (R7, R5)
+  const uint32_t d63 = pk_usat(tr, kso);             // (R6, R3)
+  const uint32_t d42 = pk_usat(tr, pjo);             // (R4, R2)
   uint32_t c = usat(pj24, v2);                          // 2 R1
   c = dot2(d42, 54u | (6u << 16), c);
   c = dot2(d63, 486u | (18u << 16), c);

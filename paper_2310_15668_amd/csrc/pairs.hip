@@ -39,7 +39,6 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------------------
 // Rows and their order.

@@ -2,7 +2,9 @@
 instruction is nor pads it: it may stand only where its result can be read by
 the next instruction.  On gfx950 a dot product's (like a matrix product's or a
 transcendental's) can not be, by another kind of instruction, for three wait
-states, so those come from the compiler's builtins.
+states, so those come from the compiler's builtins.  So do packed subtracts,
+whose operands are uniform in one kernel and the lanes' own in another: an asm
+operand is one or the other.
 """
 import glob
 import os
@@ -11,9 +13,8 @@ import re
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2310_15668_amd", "csrc")
 
-# 32-bit and packed 16-bit integer instructions without a wait of their own
-PLAIN = {"v_pk_sub_u16", "v_lshl_add_u32", "v_bcnt_u32_b32", "v_lshl_or_b32", "v_and_or_b32", "v_sub_u32_e64",
-         "v_mad_u32_u24"}
+# 32-bit integer instructions without a wait of their own
+PLAIN = {"v_lshl_add_u32", "v_bcnt_u32_b32", "v_lshl_or_b32", "v_and_or_b32", "v_sub_u32_e64", "v_mad_u32_u24"}
 # times instructions; what they compute is not used
 TIMING_ONLY = {"calibrate.hip"}
 
