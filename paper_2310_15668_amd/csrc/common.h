@@ -223,9 +223,13 @@ mochy_status exact_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, int6
 mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, int64_t c1,
                             int64_t* d_hist, unsigned long long* stats);
 
-// sampled.hip: MoCHy-A+ (hyperwedges) and MoCHy-A (hyperedges)
+// sampled.hip: MoCHy-A+ (hyperwedges); MoCHy-A (hyperedges, or with `profile`
+// those of [n0, n0 + s), a row of out each) by scanning rows, added to out
 mochy_status sampled_device(mochy_ctx* ctx, const mochy_graph* g, int64_t r, uint64_t seed,
                             int64_t n0, int64_t* d_hist);
+mochy_status scan_edges_device(mochy_ctx* ctx, const mochy_graph* g, int64_t n0, int64_t s, uint64_t seed,
+                               bool profile, unsigned long long* out);
+// edges.hip: MoCHy-A and hyperedge profiles
 mochy_status sampled_edges_device(mochy_ctx* ctx, const mochy_graph* g, int64_t s, uint64_t seed,
                                   int64_t n0, int64_t* d_hist);
 // hyperedge profiles of [c0, c1): d_prof[(c1-c0) x kHistSlots], d_prof26[(c1-c0) x 26]

@@ -23,6 +23,9 @@
 // are moved from q to the true overlap.  The second sum needs of row j only
 // its histogram by (|e_j ∩ e_k|, |e_k|), made once for all samples.  All sums
 // are of whole numbers modulo 2^64, so the counts are the same as a scan's.
+//
+// Where no row is longer than kScanDegree the rows are scanned all the same
+// (sampled.hip), and where the scratch for one sample's groups cannot be had.
 #include "classify.h"
 #include "common.h"
 #include "pairs.h"
@@ -53,6 +56,13 @@ constexpr int kNodeBlock = 1024;   // nodes a block sorts out light ones from
 constexpr unsigned kLightBlocksPerCu = 6;  // blocks of the light pairs' kernel launched per CU, at least one a sample
 constexpr int kMembers = kWave;    // members of a node's list held at a time
 constexpr int kHistW = MOCHY_MAX_EDGE;  // row histogram: |e_k| fastest, then |e_j ∩ e_k| = 1 .. |e_j|
+// Rows of up to this many neighbours are scanned: a scan is one kernel over
+// them, groups are six and their scratch.  Samples of flat hypergraphs, groups
+// and scan in ms, by the longest row: of 17 (30,000 hyperedges) 0.076 and 0.053
+// (5 samples), 0.585 and 0.206 (10,000); of 40 0.072 and 0.065, 0.66 and 0.34;
+// of 65 0.074 and 0.079, 0.85 and 0.57; of 141 0.086 and 0.134, 1.40 and 1.44;
+// of 358 0.141 and 0.383, 4.4 and 5.3.
+constexpr int32_t kScanDegree = 64;
 // scratch of one batch of samples (tables of their rows' groups)
 constexpr size_t kBatchBytes = size_t(512) << 20;
 constexpr int64_t kMaxBatch = 32768;    // grid rows
@@ -989,12 +999,12 @@ mochy_status edges_device(mochy_ctx* ctx, const mochy_graph* g, int64_t n0, int6
   const size_t fixed = size_t(g->E) * 17 + size_t(nnz) * (kHistW + 1) * 4 + size_t(g->ng) * 4 + 256;
   const size_t per = size_t(t.slots) * sizeof(uint2) + size_t(t.rows) * (4 + sizeof(uint4) + sizeof(GroupInfo)) + 32;
   int64_t batch = std::min(std::min(s, kMaxBatch), std::max<int64_t>(int64_t(kBatchBytes / per), 1));
-  mochy_status rc;
-  while ((rc = device_alloc(ctx, (void**)&blob, fixed + size_t(batch) * per)) != MOCHY_OK) {
-    if (batch == 1) return done(rc);
-    batch = (batch + 1) / 2;
+  if (g->max_deg <= kScanDegree || (ctx->test_faults & 1)) batch = 0;
+  while (batch && device_alloc(ctx, (void**)&blob, fixed + size_t(batch) * per) != MOCHY_OK) {
+    ctx->err.clear();
+    batch /= 2;
   }
-  ctx->err.clear();
+  if (batch == 0) return scan_edges_device(ctx, g, n0, s, seed, kProfile, out);
   char* at = blob;
   auto take = [&](auto*& p, size_t bytes) {
     p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(at);
