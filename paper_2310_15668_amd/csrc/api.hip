@@ -367,6 +367,18 @@ void device_free(mochy_ctx* ctx, void* p) {
   raw_free(ctx, p);
 }
 
+// No caller's kernel has more than 44 KiB of its own: below 20 KiB beside that
+// there is nothing to ask for.
+mochy_status allow_lds(mochy_ctx* ctx, const void* kernel, size_t dyn) {
+  constexpr size_t kEvery = size_t(64) << 10, kNoQuestion = size_t(20) << 10;
+  if (dyn <= kNoQuestion) return MOCHY_OK;
+  hipFuncAttributes own;
+  MOCHY_HIP(hipFuncGetAttributes(&own, kernel));
+  if (own.sharedSizeBytes + dyn > kEvery)
+    MOCHY_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, int(dyn)));
+  return MOCHY_OK;
+}
+
 // Buffers that live as long as the context.
 static mochy_status ctx_alloc(mochy_ctx* ctx, void** p, size_t bytes) {
   *p = nullptr;

@@ -245,6 +245,9 @@ extern const size_t kNoallocBytes;
 mochy_status device_alloc(mochy_ctx* ctx, void** p, size_t bytes);
 void device_free(mochy_ctx* ctx, void* p);
 void cache_release(mochy_ctx* ctx);  // frees every cached block
+// lets `kernel` be launched with `dyn` bytes of LDS beside its own where the two
+// pass the 64 KiB that every kernel may take
+mochy_status allow_lds(mochy_ctx* ctx, const void* kernel, size_t dyn);
 
 // Largest graph (hyperedges) whose row bitmap and rank table fit in LDS.
 constexpr int64_t kMaxGraphEdges = 200000;

@@ -775,9 +775,8 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
   if (c1 <= c0 || E == 0 || V == 0) return MOCHY_OK;
   const int nwE = int((g->max_graph_edges + 31) / 32);
   const size_t dyn = size_t(nwE) * 8;
-  if (dyn > 60 * 1024)
-    MOCHY_HIP(hipFuncSetAttribute((const void*)k_light_fix, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  int(dyn)));
+  mochy_status rc = allow_lds(ctx, (const void*)k_light_fix, dyn);
+  if (rc != MOCHY_OK) return rc;
   // pcount[E] | nown | owners[E] | ocount[E+1] | poff[E+1] | tmp
   const size_t tmpn = scan_tmp_elems(std::max(E, V) + 1);  // scans of E + 1 and V + 1 entries
   const size_t n64 = size_t(E) + 1 + size_t(E + 1) * 2 + tmpn;
@@ -802,8 +801,7 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
     device_free(ctx, tally);
     return s;
   };
-  mochy_status rc = device_alloc(ctx, (void**)&buf, n64 * 8 + size_t(E) * 4);
-  if (rc != MOCHY_OK) return rc;
+  if ((rc = device_alloc(ctx, (void**)&buf, n64 * 8 + size_t(E) * 4)) != MOCHY_OK) return rc;
   unsigned long long* pcount = (unsigned long long*)buf;
   unsigned long long* nown = pcount + E;
   int64_t* ocount = (int64_t*)(nown + 1);

@@ -1025,9 +1025,8 @@ mochy_status edges_device(mochy_ctx* ctx, const mochy_graph* g, int64_t n0, int6
   unsigned long long* queue = (unsigned long long*)(ctx->d_small + 496);
   const int64_t words = std::max<int64_t>((g->max_graph_edges + 31) / 32, 1);
   const size_t dyn = size_t(words + (words + kRankWords - 1) / kRankWords) * 4;
-  if (dyn > 32 * 1024)
-    MOCHY_HIP_OR(hipFuncSetAttribute((const void*)k_hs_light<kProfile>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     int(dyn)), done);
+  const mochy_status rc = allow_lds(ctx, (const void*)k_hs_light<kProfile>, dyn);
+  if (rc != MOCHY_OK) return done(rc);
   for (int64_t q0 = 0; q0 < s; q0 += batch) {
     const int64_t n = std::min(batch, s - q0);
     const bool first = q0 == 0;

@@ -655,9 +655,7 @@ mochy_status project_device(mochy_ctx* ctx, mochy_graph* g) {
   if ((rc = device_alloc(ctx, (void**)&g->rsz, size_t(std::max<int64_t>(twoW, 1)) * 2)) != MOCHY_OK) { cleanup(); return rc; }
   g->bytes += size_t(twoW) * 26;
   phase_begin(ctx, kPhRows);
-  if (2 * bm_bytes > 32 * 1024)
-    MOCHY_HIP_OR(hipFuncSetAttribute((const void*)k_proj_rows, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     int(2 * bm_bytes)), fail);
+  if ((rc = allow_lds(ctx, (const void*)k_proj_rows, 2 * bm_bytes)) != MOCHY_OK) return fail(rc);
   if (E > 0)
     k_proj_rows<<<unsigned(E), kRowThreads, 2 * bm_bytes, st>>>(
         E, g->edge_ptr, g->edge_nodes, g->node_ptr, g->node_edges, g->heavy_bit, info, hrows, g->row_graph, g->geoff,

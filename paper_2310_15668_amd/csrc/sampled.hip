@@ -352,7 +352,8 @@ mochy_status scan_edges_device(mochy_ctx* ctx, const mochy_graph* g, int64_t n0,
   int64_t batch = std::min(s, kScanBatch);
   auto scratch = [](int64_t n) { return (size_t(2 * n + 1) + scan_tmp_elems(n + 1)) * 8; };
   int64_t* sample_i = nullptr;  // [batch] | item offsets [batch + 1] | scan scratch
-  mochy_status rc;
+  mochy_status rc = allow_lds(ctx, profile ? (const void*)k_scan_rows<true> : (const void*)k_scan_rows<false>, dyn);
+  if (rc != MOCHY_OK) return rc;
   while ((rc = device_alloc(ctx, (void**)&sample_i, scratch(batch))) != MOCHY_OK) {
     if (batch == 1) return rc;
     batch /= 2;

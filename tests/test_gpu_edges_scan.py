@@ -75,3 +75,37 @@ def test_several_batches(ctx):
         assert inv == 0 and (raw431 == o431).all()
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("faults", [0, 1])
+@pytest.mark.parametrize("name,E", [("group", 146000), ("group", 148000), ("group", 200000), ("flat", 190000)])
+def test_many_hyperedges(ctx, name, E, faults):
+    """Bitmaps of a row over 146,000 to 200,000 hyperedges: with their own LDS the
+    kernels' blocks take up to 74 KB.  `group`: one row longer than is scanned."""
+    import paper_2310_15668_amd as M
+    rng = np.random.default_rng(E)
+    a = rng.integers(0, E, size=E).astype(np.int64)
+    a[:90] = E
+    nodes = np.stack([a, E + 1 + np.arange(E) % (E - 7), 2 * E + 1 + np.arange(E)], axis=1)
+    if name == "flat":
+        nodes = nodes[90:]
+    n = len(nodes)
+    h = from_edge_lists(nodes.tolist(), 3 * E + 1)
+    print(f"[gpu] {name} {E}, faults {faults}: |E|={h.num_edges}", flush=True)
+    g = M.mochy_project(ctx, h.edge_ptr, h.edge_nodes, h.num_nodes)
+    ctx.set_option(M.MOCHY_OPT_TEST_FAULTS, faults)
+    try:
+        for lo, hi in ((0, 200), (n - 200, n)):
+            p26, p431 = M.mochy_hyperedge_profiles(ctx, g, lo, hi)
+            o26, o431, inv = native.hyperedge_profiles(h, lo, hi, nthreads=8)
+            assert (inv == 0).all() and int(o431.sum()) > 0
+            assert (p431 == o431).all() and (p26 == o26).all()
+        raw431 = M.mochy_count_sampled_edges(ctx, g, 20000, 3)[2]
+        _, s431, sinv, _ = native.mochy_a_raw(h, s=20000, seed=3, nthreads=8)
+        assert sinv == 0 and (raw431 == s431).all()
+        if faults == 0:  # rows, records and the correction of as many
+            c431 = M.mochy_count_exact(ctx, g)[1]
+            assert (c431 == native.mochy_e(h, nthreads=8)[1]).all()
+    finally:
+        ctx.set_option(M.MOCHY_OPT_TEST_FAULTS, 0)
+        g.close()
