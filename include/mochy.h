@@ -142,9 +142,10 @@ const char* mochy_last_error(const mochy_ctx* ctx);
 #define MOCHY_OPT_TEST_FAULTS 10  /* for tests of the fallbacks: bit 0 makes the one-pass
                                      grouping's row-capacity allocation report
                                      MOCHY_ENOMEM, so exact counting takes the
-                                     counted-first layout, and the scratch of
-                                     hyperedge samples and profiles, so rows are
-                                     scanned; bit 1 caps the scratch of
+                                     counted-first layout, the light-pair correction's
+                                     table of overlaps, so that it goes owner by owner,
+                                     and the scratch of hyperedge samples and profiles,
+                                     so that rows are scanned; bit 1 caps the scratch of
                                      mochy_count_exact_range_noalloc at 64 KiB; bit 2
                                      makes the grouping of a batch of more than two
                                      graphs report MOCHY_ENOMEM, so mochy_profile splits

@@ -37,6 +37,7 @@ struct mochy_ctx {
   bool group_neighbours = true;       // exact counting over neighbour groups (MOCHY_OPT_GROUPS)
   bool aplus_rows = false;            // A+ by merging stored rows (MOCHY_OPT_APLUS_ROWS)
   int64_t total_mem = 0;              // device memory
+  int64_t table_bytes = 0;            // of the last light-pair correction's table of overlaps (0: none)
   int64_t group_cap_bytes = 0;        // one-pass grouping limit (MOCHY_OPT_GROUP_CAPACITY; half the
                                       // device memory from creation)
   int64_t memo_budget = int64_t(16) << 30;  // key memo arena bytes (MOCHY_OPT_MEMO_BUDGET)

@@ -29,6 +29,8 @@
 //     R5 = r5h + ls and, since e_j and e_k meet, is counted iff both are
 //     above e_i (Algorithm 2's condition).  The first is removed, the second
 //     added.
+#include <algorithm>
+
 #include "classify.h"
 #include "common.h"
 #include "pairs.h"
@@ -97,27 +99,52 @@ __global__ __launch_bounds__(256) void k_light_pairs(
 // The hyperedges of every light node, longest line-graph row first (ties: the
 // smaller id): of two of them the earlier owns the pair.  One thread per
 // incidence, which takes the place that its rank among the node's gives.
+// work: what the pairs would have scanned, row entries in [0] and in [1] their
+// share of a row of the overlap table, in kShareUnit-ths.
+constexpr unsigned long long kShareUnit = 32768;
 __global__ __launch_bounds__(256) void k_sort_members(int64_t nnz, int64_t V, const int64_t* __restrict__ node_ptr,
                                                       const int32_t* __restrict__ node_edges,
                                                       const int8_t* __restrict__ heavy_bit,
-                                                      const int64_t* __restrict__ lg_ptr, int32_t* sorted) {
+                                                      const int64_t* __restrict__ lg_ptr,
+                                                      const int32_t* __restrict__ row_graph,
+                                                      const int64_t* __restrict__ geoff, int32_t* sorted,
+                                                      unsigned long long* work) {
+  __shared__ unsigned long long s_work[2];
+  if (threadIdx.x < 2) s_work[threadIdx.x] = 0ull;
+  __syncthreads();
   const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= nnz) return;
-  int64_t lo = 0, hi = V;  // node_ptr[lo] <= t < node_ptr[lo + 1]
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (node_ptr[mid] <= t) lo = mid; else hi = mid;
+  unsigned long long entries = 0, share = 0;
+  if (t < nnz) {
+    int64_t lo = 0, hi = V;  // node_ptr[lo] <= t < node_ptr[lo + 1]
+    while (hi - lo > 1) {
+      const int64_t mid = (lo + hi) >> 1;
+      if (node_ptr[mid] <= t) lo = mid; else hi = mid;
+    }
+    if (heavy_bit[lo] < 0) {
+      const int32_t y = node_edges[t];
+      const int64_t d = lg_ptr[y + 1] - lg_ptr[y], q0 = node_ptr[lo], q1 = node_ptr[lo + 1];
+      int rank = 0;
+      for (int64_t q = q0; q < q1; ++q) {
+        const int32_t x = node_edges[q];
+        const int64_t dx = lg_ptr[x + 1] - lg_ptr[x];
+        rank += dx > d || (dx == d && x < y) ? 1 : 0;
+      }
+      sorted[q0 + rank] = y;
+      const int g = row_graph[y];
+      entries = (unsigned long long)rank * (unsigned long long)d;
+      share = entries * kShareUnit / (unsigned long long)(geoff[g + 1] - geoff[g]);
+    }
   }
-  if (heavy_bit[lo] >= 0) return;
-  const int32_t y = node_edges[t];
-  const int64_t d = lg_ptr[y + 1] - lg_ptr[y], q0 = node_ptr[lo], q1 = node_ptr[lo + 1];
-  int rank = 0;
-  for (int64_t q = q0; q < q1; ++q) {
-    const int32_t x = node_edges[q];
-    const int64_t dx = lg_ptr[x + 1] - lg_ptr[x];
-    rank += dx > d || (dx == d && x < y) ? 1 : 0;
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    entries += __shfl_xor(entries, off, kWave);
+    share += __shfl_xor(share, off, kWave);
   }
-  sorted[q0 + rank] = y;
+  if (threadIdx.x % kWave == 0) {
+    atomicAdd(&s_work[0], entries);
+    atomicAdd(&s_work[1], share);
+  }
+  __syncthreads();
+  if (threadIdx.x < 2 && s_work[threadIdx.x]) atomicAdd(&work[threadIdx.x], s_work[threadIdx.x]);
 }
 
 // The flat list of candidate pairs, in units of kOwners slots: a light node w's
@@ -172,10 +199,11 @@ __global__ __launch_bounds__(256) void k_light_slots(
 }
 
 // Slots of every light node's units (0 for heavy ones), the input of the flat
-// list's offsets; cnt[V] = 0.
+// list's offsets; cnt[V] = 0.  Clears k_sort_members' work.
 __global__ void k_pair_slots(int64_t V, const int64_t* __restrict__ node_ptr,
-                             const int8_t* __restrict__ heavy_bit, int64_t* cnt) {
+                             const int8_t* __restrict__ heavy_bit, int64_t* cnt, unsigned long long* work) {
   const int64_t w = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (w < 2) work[w] = 0ull;
   if (w > V) return;
   cnt[w] = w < V && heavy_bit[w] < 0 ? kOwners * node_units(node_ptr[w + 1] - node_ptr[w]) : 0;
 }
@@ -429,6 +457,28 @@ constexpr int64_t kXcdUnits = 65536;  // by waves, a graph of as many units has 
 constexpr int kDenseCopies = 4;
 constexpr uint32_t kDenseFlush = 1u << 24;  // entries of a wave between flushes (8 waves share a counter)
 constexpr int kOverlapChunk = 32768;  // bytes of a row formed in LDS at a time
+
+// The table takes a write of all its bytes and, for each entry scanned, a read
+// in a row that other pairs may have left in the caches; owner by owner the same
+// answer is a bit in LDS, after a sort of the pairs by owner and with a row of
+// bits to build for each.  Tables of up to kSmallTable a graph, and kSmallTables
+// in all, always pay.  Larger ones do where the scanned rows fill a kDenseRow-th of the table's or more and hold
+// as many entries as the table bytes.  Correction in ms, table and owner by owner
+// (the scanned rows' share; the table):
+//   10,000 hyperedges, flat   (0.004, 0.1 GB)  0.20  0.34
+//   20,000, exponent 0.8      (0.014, 0.4 GB)  0.86  1.01
+//   9 of 20,000, exponent 0.3 (0.002, 3.6 GB)  2.6   3.1
+//   33 of 6,000, exponent 0.8 (0.02, 1.2 GB)   2.4   3.8
+//   17,636, exponent 1        (0.09, 0.3 GB)   1.22  1.70
+//   30,000, exponent 0.9      (0.09, 0.7 GB)   8.3   12.1
+//   50,000, exponent 0.9      (0.04, 2.2 GB)   14.3  17.0
+//   85,311, exponent 1        (0.08, 7.3 GB)   56.6  84.7
+//   30,000, exponent 0.5      (0.006, 0.9 GB)  3.7   2.2
+//   50,000, exponent 0.8      (0.013, 2.4 GB)  8.9   6.1
+//   100,000, exponent 0.7     (0.002, 10 GB)   12.3  4.7
+//   100,000, flat             (0.003, 10 GB)   37.7  11.9
+constexpr size_t kSmallTable = size_t(512) << 20, kSmallTables = size_t(8) << 30;
+constexpr unsigned long long kDenseRow = 32;
 
 // Per graph: where its rows of W start, their stride (a multiple of 16) and
 // the first centre; one thread per graph.
@@ -815,9 +865,10 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
   // carved from a caller's arena); otherwise a counting pass now and a
   // filling pass once the owners' offsets are known
   int64_t ncand = 0;
+  unsigned long long* const work = (unsigned long long*)(ctx->d_small + 504);  // [2]
   if (!ctx->arena && !(ctx->test_faults & 8)) {
     if ((rc = device_alloc(ctx, (void**)&noff, size_t(V + 1) * 8)) != MOCHY_OK) return done(rc);
-    k_pair_slots<<<blocks(V + 1, 256), 256, 0, st>>>(V, g->node_ptr, g->heavy_bit, noff);
+    k_pair_slots<<<blocks(V + 1, 256), 256, 0, st>>>(V, g->node_ptr, g->heavy_bit, noff, work);
     launch_exclusive_scan_i64(noff, noff, V + 1, tmp, st);
     MOCHY_HIP_OR(hipMemcpyAsync(ctx->h_small + 503, noff + V, 8, hipMemcpyDeviceToHost, st), done);
     MOCHY_HIP_OR(hipStreamSynchronize(st), done);
@@ -829,40 +880,52 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
       ctx->err.clear();
     }
     if (flat)
-      k_sort_members<<<blocks(g->nnz, 256), 256, 0, st>>>(g->nnz, V, g->node_ptr, g->node_edges, g->heavy_bit,
-                                                          g->lg_ptr, sorted);
+      k_sort_members<<<blocks(g->nnz, 256), 256, 0, st>>>(g->nnz, V, g->node_ptr, g->node_edges, g->heavy_bit, g->lg_ptr,
+                                                          g->row_graph, g->geoff, sorted, work);
   }
-  // the overlap table where it takes at most a sixth of the device memory
-  // (40 GB for the largest graph) and can be allocated
+  // the overlap table: where it takes at most a sixth of the device memory (40 GB
+  // for the largest graph), pays for itself and can be allocated
   uint8_t* W = nullptr;
   OverlapTable* tab = nullptr;
+  const int64_t nblocks = std::min<int64_t>(int64_t(ctx->num_cus) * 4, (ncand + 4 * kOwners - 1) / (4 * kOwners));
+  const size_t qbytes = size_t(g->ng) * kXcds * 4;
   if (flat) {
-    size_t wbytes = 0;
+    size_t wbytes = 0, most = 0;
     for (int x = 0; x < g->ng; ++x) {
       const int64_t e0 = g->h_geoff[x], e1 = g->h_geoff[x + 1];
       const int64_t width = std::max<int64_t>(std::min(e1, c1) - std::max(e0, c0), 0);
-      wbytes += size_t(e1 - e0) * size_t((width + 15) & ~int64_t(15));
+      const size_t b = size_t(e1 - e0) * size_t((width + 15) & ~int64_t(15));
+      wbytes += b;
+      most = std::max(most, b);
     }
-    if (wbytes > 0 && wbytes <= size_t(ctx->total_mem / 6) &&
-        (device_alloc(ctx, (void**)&tab, size_t(g->ng) * sizeof(OverlapTable)) != MOCHY_OK ||
-         device_alloc(ctx, (void**)&W, wbytes) != MOCHY_OK)) {
-      device_free(ctx, tab);  // no room: owner by owner instead
+    bool pays = wbytes > 0 && wbytes <= size_t(ctx->total_mem / 6) && !(ctx->test_faults & 1);
+    if (pays && (most > kSmallTable || wbytes > kSmallTables)) {
+      MOCHY_HIP_OR(hipMemcpyAsync(ctx->h_small + 504, work, 16, hipMemcpyDeviceToHost, st), done);
+      MOCHY_HIP_OR(hipStreamSynchronize(st), done);
+      // a range's columns of the rows are as many of their entries
+      const double entries = double(ctx->h_small[504]) * double(c1 - c0) / double(E);
+      pays = double(ctx->h_small[505]) * double(kDenseRow) >= double(ncand) * double(kShareUnit) &&
+             entries >= double(wbytes);
+    }
+    if (pays && (device_alloc(ctx, (void**)&tally, size_t(nblocks) * 24 + qbytes) != MOCHY_OK ||
+                 device_alloc(ctx, (void**)&tab, size_t(g->ng) * sizeof(OverlapTable)) != MOCHY_OK ||
+                 device_alloc(ctx, (void**)&W, wbytes) != MOCHY_OK)) {
+      device_free(ctx, tally);  // no room: owner by owner instead
+      device_free(ctx, tab);
+      tally = nullptr;
       tab = nullptr;
       W = nullptr;
       ctx->err.clear();
     }
+    if (W) ctx->table_bytes = int64_t(wbytes);
   }
   if (W) {
-    const int64_t nblocks = std::min<int64_t>(int64_t(ctx->num_cus) * 4, (ncand + 4 * kOwners - 1) / (4 * kOwners));
-    uint32_t* queues = nullptr;
     auto dense_done = [&](mochy_status s) {
       device_free(ctx, W);
       device_free(ctx, tab);
       return done(s);
     };
-    const size_t qbytes = size_t(g->ng) * kXcds * 4;
-    if ((rc = device_alloc(ctx, (void**)&tally, size_t(nblocks) * 24 + qbytes)) != MOCHY_OK) return dense_done(rc);
-    queues = (uint32_t*)(tally + nblocks * 3);
+    uint32_t* const queues = (uint32_t*)(tally + nblocks * 3);
     launch_fill_u32(queues, 0u, qbytes, st);
     k_light_slots<<<blocks(ncand, 256), 256, 0, st>>>(V, ncand, g->node_ptr, sorted, g->heavy_bit, g->edge_ptr,
                                                       g->edge_nodes, nullptr, noff, flat);

@@ -949,6 +949,7 @@ mochy_status exact_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, int6
   unsigned long long* stats = (unsigned long long*)(ctx->d_small + kExactStatsSlot);
   launch_fill_u32(d_hist, 0u, size_t(ng) * kHistSlots * 8, st);
   launch_fill_u32(stats, 0u, kStBatches * 8, st);
+  ctx->table_bytes = 0;
   if (c1 <= c0 || g->max_deg < 2) return MOCHY_OK;
   if (g->max_deg >= (1 << 24)) {  // group sizes are multiplied as 24-bit numbers
     ctx->err = "a line-graph row of 2^24 or more neighbours";

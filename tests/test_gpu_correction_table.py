@@ -1,0 +1,88 @@
+"""When the light-pair correction takes its table of overlaps: not for a flat
+hypergraph whose table would be far more than the rows scanned, and the pairs
+then go owner by owner from the list of candidates; the counts are the
+oracle's either way."""
+import numpy as np
+import pytest
+
+from oracle import native
+from workloads import from_edge_lists, powerlaw_hypergraph
+
+pytestmark = pytest.mark.gpu
+
+
+def _flat(E, V, size, seed):
+    rows = np.unique(np.sort(np.random.default_rng(seed).integers(0, V, size=(E, size)), axis=1), axis=0)
+    rows = rows[(np.diff(rows, axis=1) > 0).all(axis=1)]
+    return from_edge_lists(rows[np.random.default_rng(seed + 1).permutation(len(rows))].tolist(), V)
+
+
+def _check(M, ctx, h, ranges=(None,)):
+    g = M.mochy_project(ctx, h.edge_ptr, h.edge_nodes, h.num_nodes)
+    try:
+        stats = []
+        for r in ranges:
+            c0, c1 = r or (0, h.num_edges)
+            c26, c431 = M.mochy_count_exact_range(ctx, g, c0, c1)
+            r26, r431, inv = native.mochy_e(h, c0, c1, nthreads=8)
+            assert inv == 0
+            assert (c431 == r431).all() and (c26 == r26).all(), (c0, c1)
+            stats.append(M.mochy_exact_stats(ctx))
+        return stats
+    finally:
+        g.close()
+
+
+@pytest.mark.parametrize("E,V,size", [(22000, 9000, 3), (26000, 9000, 3), (100000, 200000, 3), (60000, 9000, 2)])
+def test_flat(E, V, size):
+    """Tables of 0.48 GB (taken) to 10 GB: what the context keeps afterwards tells."""
+    import torch
+    import paper_2310_15668_amd as M
+    h = _flat(E, V, size, 5)
+    table = h.num_edges * ((h.num_edges + 15) // 16 * 16)
+    print(f"[gpu] flat |E|={h.num_edges}, table {table >> 20} MiB", flush=True)
+    with M.Context(0) as ctx:
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info(0)[0]
+        st, *_ = _check(M, ctx, h, (None, (h.num_edges // 2, h.num_edges // 2 + 300)))
+        held = before - torch.cuda.mem_get_info(0)[0]
+        assert st["light_pairs"] > 1000 and st["fix_changed"] > 0
+        if table > 512 << 20:
+            assert held < table // 2, (held, table)
+
+
+CASES = {
+    "sparse": (lambda: powerlaw_hypergraph(4000, 3000, 1, 6, 2.5, 0.3, seed=7), (None, (0, 1), (1200, 1900))),
+    "many-light": (lambda: powerlaw_hypergraph(3000, 2500, 1, 25, 2.2, 0.4, seed=3), (None, (700, 1300))),
+    "skewed": (lambda: powerlaw_hypergraph(900, 1500, 2, 12, 2.5, 0.9, seed=4), (None, (700, 701))),
+    "one-owner": (lambda: from_edge_lists([[x, 70] for x in range(70)] + [[0, 71], [1, 71], [2, 3]], 72), (None,)),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_listed_without_table(name):
+    """The table refused (fault bit 0), the list of candidates kept."""
+    import paper_2310_15668_amd as M
+    make, ranges = CASES[name]
+    h = make()
+    print(f"[gpu] {name}: |E|={h.num_edges}", flush=True)
+    with M.Context(0) as ctx:
+        with_table = _check(M, ctx, h, ranges)
+        ctx.set_option(M.MOCHY_OPT_TEST_FAULTS, 1)
+        without = _check(M, ctx, h, ranges)
+        for a, b in zip(with_table, without):
+            for k in ("light_pairs", "fix_scanned", "fix_centres", "fix_changed"):
+                assert a[k] == b[k], k
+
+
+def test_batch_without_table():
+    import paper_2310_15668_amd as M
+    graphs = [powerlaw_hypergraph(2000, 1500, 1, 12, 2.2, 0.5, seed=7), from_edge_lists([[0, 1], [2]], 3),
+              powerlaw_hypergraph(700, 900, 2, 9, 2.5, 0.2, seed=8)]
+    print(f"[gpu] batch |E|={[h.num_edges for h in graphs]}", flush=True)
+    with M.Context(0) as ctx:
+        ctx.set_option(M.MOCHY_OPT_TEST_FAULTS, 1)
+        counts = M.mochy_profile(ctx, [(h.edge_ptr, h.edge_nodes, h.num_nodes) for h in graphs])[0]
+    for x, h in enumerate(graphs):
+        r26, r431, inv = native.mochy_e(h, nthreads=8)
+        assert inv == 0 and (counts[x, :26] == r26).all() and (counts[x, 26:] == r431).all(), x
