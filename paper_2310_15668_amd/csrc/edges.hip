@@ -527,7 +527,7 @@ __global__ __launch_bounds__(kPairThreads) void k_hs_pairs(
         rk = grec[k];
         fk = ginfo[k];
       }
-      const uint32_t aks2 = 2u * (a - (fk.kso & 0xffffu)) - 4u;
+      const uint32_t aks2 = pair_aks2(a - (fk.kso & 0xffffu));
       const uint32_t far_k = fk.far >> 16 | fk.far << 16;
       const uint32_t wave_nk = uint32_t(wave_sum_i64(int64_t(fk.n)));
       if (lane == 0) s_nk[wave] = wave_nk;

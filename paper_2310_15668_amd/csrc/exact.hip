@@ -206,7 +206,7 @@ __global__ __launch_bounds__(1024) void k_schedule(int64_t c0, int64_t c1, const
 // The lane's k as the walks take it.
 struct LaneSide {
   uint32_t m, hl, hh, kso;  // masks; |e_i ∩ e_k| | outside count << 16
-  uint32_t aks2;            // 2 (|e_i| - |e_i ∩ e_k|) - 4
+  uint32_t aks2;            // pair_aks2 of |e_i| - |e_i ∩ e_k|
   uint32_t aksd;            // 2 (|e_i| - |e_i ∩ e_k|)
   uint32_t open;            // its digits R6 and R3 of a disjoint pair, and those of t = R5 = 0
   uint32_t one;             // 1, 0 past the row's end
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(kMainThreads) void k_exact_main(
         k.hh = rk.w;
         k.kso = ks | ko << 16;
         k.aksd = 2u * (a - ks);
-        k.aks2 = k.aksd - 4u;
+        k.aks2 = pair_aks2(a - ks);
         k.open = 2u * 1458u + 2u * 162u + 486u * usat(2u, ks) + 18u * usat(2u, ko);
         k.one = valid ? 1u : 0u;
         k.kp = kp;

@@ -52,8 +52,7 @@ __device__ __forceinline__ uint32_t dot2(uint32_t a, uint32_t b, uint32_t c) {
 __device__ __forceinline__ uint32_t pair_rcode2(uint32_t t2, uint32_t tr, uint32_t aks2, uint32_t jy,
                                                 uint32_t kso) {
   const uint32_t pjo = jy & 0x00ff00ffu, pj24 = (jy >> 8) & 0xffu;
-  uint32_t v2;  // 2 (aks + t) = 2 t2 + aks2, one shift-add
-  asm("v_lshl_add_u32 %0, %1, 1, %2" : "=v"(v2) : "v"(t2), "v"(aks2));
+  const uint32_t v2 = 2u * t2 + aks2;  // 2 (aks + t), one shift-add
   const uint32_t d75 = pk_usat(0x00040004u, tr);     // (R7, R5)
   const uint32_t d63 = pk_usat(tr, kso);             // (R6, R3)
   const uint32_t d42 = pk_usat(tr, pjo);             // (R4, R2)
@@ -63,15 +62,16 @@ __device__ __forceinline__ uint32_t pair_rcode2(uint32_t t2, uint32_t tr, uint32
   return dot2(d75, 1458u | (162u << 16), c);
 }
 
-// t + 2 and r5 + 2 of a pair from its mask intersections (population counts
-// with the constant added in the same instruction; r5 over two words).
-// tr = (t + 2) | (r5 + 2) << 16.
+// t + 2 and r5 + 2 of a pair from its mask intersections: tr = (t + 2) |
+// (r5 + 2) << 16, both constants added with the population count of xm, so t2 =
+// t + 2 + kT2Bias, which pair_aks2 takes off again.
+constexpr uint32_t kT2Bias = 2u << 16;
 __device__ __forceinline__ void pair_counts(uint32_t xm, uint32_t xl, uint32_t xh, uint32_t& t2, uint32_t& tr) {
-  t2 = uint32_t(__popc(xm)) + 2u;
-  uint32_t r2;
-  asm("v_bcnt_u32_b32 %0, %1, 2\n\tv_bcnt_u32_b32 %0, %2, %0" : "=&v"(r2) : "v"(xl), "v"(xh));
-  asm("v_lshl_or_b32 %0, %1, 16, %2" : "=v"(tr) : "v"(r2), "v"(t2));
+  t2 = uint32_t(__popc(xm)) + (kT2Bias | 2u);
+  tr = ((uint32_t(__popc(xl)) + uint32_t(__popc(xh))) << 16) + t2;
 }
+// pair_rcode2's aks2 beside it: aks = |e_i| - |e_i ∩ e_k|.
+__device__ __forceinline__ uint32_t pair_aks2(uint32_t aks) { return 2u * aks - 4u - 2u * kT2Bias; }
 
 // The histogram word at a byte offset the class table gives.
 __device__ __forceinline__ unsigned long long* hist_at(unsigned long long* hist, uint32_t off) {
@@ -165,7 +165,7 @@ __device__ __forceinline__ void gwalk(const uint4* __restrict__ grow, const type
   asm volatile("" : "+v"(z));
   using C = typename GroupCount<kNarrow>::T;
   const C* gc = gc0 + z;
-  const uint32_t aks2 = 2u * aks - 4u;
+  const uint32_t aks2 = pair_aks2(aks);
   const uint32_t kso = k.s | (k.o << 16);
   const uint32_t kn16 = kn << 16;
   int j = j0;

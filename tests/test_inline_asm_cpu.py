@@ -14,7 +14,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2310_15668_amd", "csrc")
 
 # 32-bit integer instructions without a wait of their own
-PLAIN = {"v_lshl_add_u32", "v_bcnt_u32_b32", "v_lshl_or_b32", "v_and_or_b32", "v_sub_u32_e64", "v_mad_u32_u24"}
+PLAIN = {"v_and_or_b32", "v_sub_u32_e64", "v_mad_u32_u24"}
 # times instructions; what they compute is not used
 TIMING_ONLY = {"calibrate.hip"}
 
