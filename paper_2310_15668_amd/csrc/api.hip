@@ -1001,8 +1001,8 @@ static mochy_status build_set(mochy_ctx* ctx, const mochy_csr* graphs, int32_t g
 // Exact counts of graphs [g0, g1) into d_all[g][kHistSlots], in consecutive
 // sub-batches.  The first takes graphs up to kFirstBatchEdges hyperedges;
 // the hyperwedges and device bytes per hyperedge that each one needed (its
-// graph set, and row capacity for one-pass grouping: 24 B per row entry)
-// size the next: at most three quarters of the memory then free (including
+// graph set, row capacity for one-pass grouping, 24 B per row entry, and the
+// light-pair correction's table) size the next: at most three quarters of the memory then free (including
 // this context's cached buffers), row capacity within the one-pass limit,
 // and at most kBatchWedges hyperwedges, about what fills the device (a
 // hypergraph of that size already keeps every kernel's grid full, and a
@@ -1029,7 +1029,7 @@ static mochy_status profile_counts(mochy_ctx* ctx, const mochy_csr* graphs, int3
     if (rc == MOCHY_OK) {
       rc = exact_device(ctx, set, 0, set->E, d_all + int64_t(a) * kHistSlots);
       if (set->E > 0) {
-        per_edge = (double(set->bytes) + 48.0 * double(set->W)) / double(set->E);
+        per_edge = (double(set->bytes) + 48.0 * double(set->W) + double(ctx->table_bytes)) / double(set->E);
         wedges_per_edge = double(set->W) / double(set->E);
       }
       mochy_graph_free(set);

@@ -23,22 +23,57 @@ import numpy as np
 from . import _lib
 
 
+HEAVY_NODES = 64            # of a graph: the correction's pairs share none of them
+SMALL_TABLE = 512 << 20     # bytes: tables of overlaps up to this are always made
+CANDIDATE_LIST = 4 << 30    # bytes: the longest list of candidate pairs; no table beyond it
+
+
+def _correction_bytes(E: int, ptr, nodes, deg) -> tuple:
+    """Upper bounds for the light-pair correction of one graph: (bytes of its
+    lists, of its table of overlaps, row entries that its pairs scan).  Light
+    nodes are those past the 64 of highest degree, in two hyperedges or more."""
+    light = np.sort(deg)[::-1][HEAVY_NODES:]
+    light = light[light >= 2]
+    if light.size == 0:
+        return 0, 0, 0
+    pairs = int((light * (light - 1) // 2).sum())
+    # candidate pairs in units of four owners, 8 bytes each; the members, 4 bytes
+    # an incidence; owner by owner a partner of 4 bytes for each pair and work
+    # items of 28 bytes for every 128
+    chunks = (light + 2) // 4
+    slots = 4 * int((chunks * (light - 1) - 2 * chunks * (chunks - 1)).sum())
+    lists = 8 * (len(deg) + 1) + 80 * E + 5 * pairs
+    if 8 * slots > CANDIDATE_LIST:
+        return lists, 0, 0
+    longest = min(E - 1, int(np.add.reduceat(deg[np.asarray(nodes)] - 1, np.asarray(ptr)[:-1]).max()))
+    return lists + 4 * len(nodes) + 8 * slots, E * ((E + 15) // 16 * 16), pairs * longest
+
+
 def request_bytes(graphs) -> int:
     """Upper bound of the device memory a request holds while it runs.
 
-    Per graph: incidence and transpose, per-row arrays, and the line graph
+    Per graph: incidence and transpose, per-row arrays, the line graph
     (4-byte column + 16-byte record + 4-byte record mask + 2-byte size word per
     row entry, and the exact counting's neighbour groups, 24 bytes per row
-    entry, with |wedges| bounded by sum_v C(deg(v), 2)).
+    entry, with |wedges| bounded by sum_v C(deg(v), 2)), and the lists of the
+    light-pair correction.  Its tables of overlaps: a byte for each pair of
+    hyperedges, where the graphs' are above SMALL_TABLE only if the pairs scan
+    as many row entries.
     """
-    total = 0
+    total = small = tables = entries = 0
     for ptr, nodes, num_nodes in graphs:
         E = len(ptr) - 1
         nnz = int(ptr[-1]) if E > 0 else 0
         deg = np.bincount(np.asarray(nodes), minlength=int(num_nodes)).astype(np.int64)
         wedges = int((deg * (deg - 1) // 2).sum())
         total += 16 * (E + 1) + 8 * nnz + 9 * (int(num_nodes) + 1) + 40 * E + 2 * wedges * 50
-    return total
+        if E > 0:
+            lists, table, scanned = _correction_bytes(E, ptr, nodes, deg)
+            total += lists
+            tables += table
+            small += table if table <= SMALL_TABLE else 0
+            entries += scanned
+    return total + min(tables, max(small, entries))
 
 
 class Admission:
