@@ -19,8 +19,8 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libmochy.so")
 OBJDIR = os.path.join(HERE, "_build")
 
-SOURCES = ["patterns.cpp", "scan.hip", "project.hip", "exact.hip", "pairs.hip", "edges.hip", "correct.hip", "sampled.hip",
-           "free.hip", "memo.hip", "calibrate.hip", "noalloc.hip", "api.hip"]
+SOURCES = ["patterns.cpp", "cache.cpp", "scan.hip", "project.hip", "exact.hip", "pairs.hip", "edges.hip", "correct.hip",
+           "sampled.hip", "free.hip", "memo.hip", "calibrate.hip", "noalloc.hip", "api.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -43,7 +43,7 @@ struct mochy_ctx {
   int64_t memo_budget = int64_t(16) << 30;  // key memo arena bytes (MOCHY_OPT_MEMO_BUDGET)
   bool memo_all = false;              // memoize every key that fits (MOCHY_OPT_MEMO_ALL)
   bool memo_pool = false;             // always restrict other-side skips (MOCHY_OPT_MEMO_POOL)
-  int batch_launch = 0;               // pair kernel over a batch: 0 size rule, 1 one launch, 2 per graph
+  int batch_launch = 0;               // pair kernels over a batch: 0 and 1 one launch, 2 per graph
   int pair_blocks = 8;                // pair kernel waves per CU / 4 (MOCHY_OPT_PAIR_BLOCKS)
   int test_faults = 0;                // MOCHY_OPT_TEST_FAULTS bits (forced fallbacks)
   // allocation-free calls: device_alloc carves from this device's static
@@ -54,9 +54,9 @@ struct mochy_ctx {
   // freed buffers kept for reuse on this
   // context's stream (MOCHY_OPT_CACHE_BYTES): size -> block, and the size of
   // every block handed out from or destined for the cache
+  std::mutex cache_mu;                // guards the four below
   int64_t cache_limit = 0;            // bytes (half the device memory from creation)
   int64_t cache_bytes = 0;
-  std::mutex cache_mu;                // guards the cache
   std::multimap<size_t, void*> cache_free;
   std::unordered_map<void*, size_t> cache_live;
   int num_cus = 0;
@@ -242,10 +242,15 @@ mochy_status profiles_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, i
 mochy_status noalloc_setup(mochy_ctx* ctx);
 extern const size_t kNoallocBytes;
 
-// api.hip helpers: allocation and release ordered on the context stream
+// cache.cpp: allocation and release ordered on the context stream, from any
+// thread
 mochy_status device_alloc(mochy_ctx* ctx, void** p, size_t bytes);
 void device_free(mochy_ctx* ctx, void* p);
 void cache_release(mochy_ctx* ctx);  // frees every cached block
+void cache_set_limit(mochy_ctx* ctx, int64_t bytes);
+int64_t cache_held(mochy_ctx* ctx);  // bytes of the cached blocks
+
+// api.hip
 // lets `kernel` be launched with `dyn` bytes of LDS beside its own where the two
 // pass the 64 KiB that every kernel may take
 mochy_status allow_lds(mochy_ctx* ctx, const void* kernel, size_t dyn);
