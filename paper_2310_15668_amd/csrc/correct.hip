@@ -477,11 +477,21 @@ constexpr int kOverlapChunk = 32768;  // bytes of a row formed in LDS at a time
 //   50,000, exponent 0.8      (0.013, 2.4 GB)  8.9   6.1
 //   100,000, exponent 0.7     (0.002, 10 GB)   12.3  4.7
 //   100,000, flat             (0.003, 10 GB)   37.7  11.9
+// Sets of more than kFewGraphs graphs of fewer than kGraphSlots candidate slots
+// each (the kernel on the tables goes from graph to graph) have none:
+//   9 of 300 hyperedges (1,100 slots)     0.09  0.15
+//   33 of 500 (2,480)                     0.25  0.22
+//   1,000 of 200 (530)                    2.3   0.92
+//   3,000 of 100 (78)                     5.9   0.78
+//   100 of 1,000 (6,110)                  0.66  0.85
+//   1,000 of 1,000 (6,100)                6.2   7.8
 constexpr size_t kSmallTable = size_t(512) << 20, kSmallTables = size_t(8) << 30;
+constexpr int kFewGraphs = 16;
+constexpr int64_t kGraphSlots = 4096;
 constexpr unsigned long long kDenseRow = 32;
 
-// Per graph: where its rows of W start, their stride (a multiple of 16) and
-// the first centre; one thread per graph.
+// Per graph: where its rows of W start, their stride (a multiple of 16) and the
+// first centre; one block, a run of graphs to each thread.
 struct OverlapTable {
   int64_t off;
   int32_t first, width, stride;
@@ -495,10 +505,20 @@ __device__ __forceinline__ OverlapTable overlap_of(int64_t e0, int64_t e1, int64
   t.stride = (t.width + 15) & ~15;
   return t;
 }
-__global__ void k_overlap_offsets(int ng, const int64_t* __restrict__ geoff, int64_t c0, int64_t c1,
-                                  OverlapTable* tab) {
-  int64_t at = 0;
-  for (int g = 0; g < ng; ++g) {
+constexpr int kOffsetThreads = 256;
+__global__ __launch_bounds__(kOffsetThreads) void k_overlap_offsets(int ng, const int64_t* __restrict__ geoff,
+                                                                    int64_t c0, int64_t c1, OverlapTable* tab) {
+  __shared__ int64_t part[kOffsetThreads];
+  const int tid = int(threadIdx.x), per = (ng + kOffsetThreads - 1) / kOffsetThreads;
+  const int g0 = min(ng, tid * per), g1 = min(ng, g0 + per);
+  int64_t sum = 0;
+  for (int g = g0; g < g1; ++g)
+    sum += (geoff[g + 1] - geoff[g]) * overlap_of(geoff[g], geoff[g + 1], c0, c1).stride;
+  part[tid] = sum;
+  __syncthreads();
+  int64_t at = 0;  // of the threads before
+  for (int x = 0; x < tid; ++x) at += part[x];
+  for (int g = g0; g < g1; ++g) {
     OverlapTable t = overlap_of(geoff[g], geoff[g + 1], c0, c1);
     t.off = at;
     at += (geoff[g + 1] - geoff[g]) * t.stride;
@@ -566,7 +586,7 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(6
     const OverlapTable t = tab[g];
     const bool by_wave = t.stride >= kLongStride;
     const uint32_t nq = by_wave && units >= kXcdUnits ? kXcds : 1u, per = (units + nq - 1u) / nq;
-    const uint32_t bunits = 
+    const uint32_t bunits =
         uint32_t(min(max(int64_t(units) * ng / (gridDim.x * 2), int64_t(kDenseThreads / kWave)), int64_t(kBlockUnits)));
     uint32_t* queue = queues + size_t(g) * kXcds;
     if (threadIdx.x == 0)
@@ -898,7 +918,8 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
       wbytes += b;
       most = std::max(most, b);
     }
-    bool pays = wbytes > 0 && wbytes <= size_t(ctx->total_mem / 6) && !(ctx->test_faults & 1);
+    bool pays = wbytes > 0 && wbytes <= size_t(ctx->total_mem / 6) && !(ctx->test_faults & 1) &&
+                (g->ng <= kFewGraphs || ncand >= g->ng * kGraphSlots);
     if (pays && (most > kSmallTable || wbytes > kSmallTables)) {
       MOCHY_HIP_OR(hipMemcpyAsync(ctx->h_small + 504, work, 16, hipMemcpyDeviceToHost, st), done);
       MOCHY_HIP_OR(hipStreamSynchronize(st), done);
@@ -929,7 +950,7 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
     launch_fill_u32(queues, 0u, qbytes, st);
     k_light_slots<<<blocks(ncand, 256), 256, 0, st>>>(V, ncand, g->node_ptr, sorted, g->heavy_bit, g->edge_ptr,
                                                       g->edge_nodes, nullptr, noff, flat);
-    k_overlap_offsets<<<1, 1, 0, st>>>(g->ng, g->geoff, c0, c1, tab);
+    k_overlap_offsets<<<1, kOffsetThreads, 0, st>>>(g->ng, g->geoff, c0, c1, tab);
     k_overlap_rows<<<unsigned(E), 256, 0, st>>>(g->row_graph, g->geoff, tab, g->lg_ptr, g->lg_col, g->rsz, W);
     phase_begin(ctx, kPhFix);
     k_light_dense<<<unsigned(nblocks), kDenseThreads, 0, st>>>(

@@ -86,3 +86,23 @@ def test_batch_without_table():
     for x, h in enumerate(graphs):
         r26, r431, inv = native.mochy_e(h, nthreads=8)
         assert inv == 0 and (counts[x, :26] == r26).all() and (counts[x, 26:] == r431).all(), x
+
+
+# sets on either side of the line for many graphs (4,096 candidate slots a graph:
+# some 1,170 hyperedges here), and of more graphs than the table's offsets have
+# threads
+@pytest.mark.parametrize("n,E", [(16, 200), (17, 200), (600, 180), (20, 1000), (20, 1400), (257, 1500), (513, 1500)])
+def test_many_graphs(n, E):
+    import paper_2310_15668_amd as M
+    kinds = [powerlaw_hypergraph(E // 2 + x % 7 if x % 5 else 30, E - x % 9 if x % 6 else 12, 2, 4, 2.5, 0.5, seed=x)
+             for x in range(11)]
+    refs = [native.mochy_e(h, nthreads=8) for h in kinds]
+    order = [(5 * x + x // 11) % 11 for x in range(n)]
+    print(f"[gpu] {n} graphs, {sum(kinds[k].num_edges for k in order)} hyperedges", flush=True)
+    with M.Context(0) as ctx:
+        counts = M.mochy_profile(ctx, [(kinds[k].edge_ptr, kinds[k].edge_nodes, kinds[k].num_nodes) for k in order])[0]
+        st = M.mochy_exact_stats(ctx)
+    assert st["light_pairs"] > 0 and st["fix_changed"] > 0
+    for x, k in enumerate(order):
+        r26, r431, inv = refs[k]
+        assert inv == 0 and (counts[x, :26] == r26).all() and (counts[x, 26:] == r431).all(), x
