@@ -700,7 +700,7 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(8, 8)
   __syncthreads();
   const int lane = threadIdx.x & (kWave - 1);
   unsigned long long* myhist = hist + (lane & (kGCopies - 1)) * kGStride;
-  visit_graphs(I, [&](int g, const ItemRange& items) {
+  visit_many_graphs(I, [&](int g, const ItemRange& items) {
     int32_t i;
     int b;
     while (next_item(items, lane, i, b)) {
