@@ -154,7 +154,9 @@ const char* mochy_last_error(const mochy_ctx* ctx);
                                      counting and a filling pass; bit 4 makes the pair
                                      kernel form 48-bit pair weights from unpacked group
                                      counts, as for graphs whose line-graph degree
-                                     reaches 2^16 (default 0);
+                                     reaches 2^16, and 32-bit counters (every-pair
+                                     kernel, light-pair correction) emptied after a few
+                                     hundred additions (default 0);
                                      same counts */
 mochy_status mochy_ctx_set_option(mochy_ctx* ctx, int32_t option, int64_t value);
 

@@ -455,7 +455,9 @@ constexpr int kDensePull = 2;
 constexpr uint32_t kBlockUnits = 64;
 constexpr int64_t kXcdUnits = 65536;  // by waves, a graph of as many units has a queue per XCD
 constexpr int kDenseCopies = 4;
-constexpr uint32_t kDenseFlush = 1u << 24;  // entries of a wave between flushes (8 waves share a counter)
+// entries of a wave between flushes (8 waves share a counter); few of them for
+// tests of the flush
+constexpr uint32_t kDenseFlush = 1u << 24, kDenseFlushTest = 256;
 constexpr int kOverlapChunk = 32768;  // bytes of a row formed in LDS at a time
 
 // The table takes a write of all its bytes and, for each entry scanned, a read
@@ -566,7 +568,8 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(6
     const uint8_t* __restrict__ W, const int64_t* __restrict__ edge_ptr, const int32_t* __restrict__ edge_nodes,
     const int8_t* __restrict__ heavy_bit, const int64_t* __restrict__ lg_ptr, const int32_t* __restrict__ lg_col,
     const int32_t* __restrict__ up_first, const uint32_t* __restrict__ recm, const uint16_t* __restrict__ rsz,
-    const uint16_t* __restrict__ code_to_id3, unsigned long long* hist_out, unsigned long long* tally) {
+    const uint16_t* __restrict__ code_to_id3, unsigned long long* hist_out, unsigned long long* tally,
+    uint32_t flush) {
   __shared__ uint16_t lut[kNumCodes];              // by reversed code: word of the id in a histogram copy
   __shared__ int32_t hist[kDenseCopies * kGStride];
   __shared__ unsigned long long s_tally[3];        // entries scanned, centres examined, centres reclassified
@@ -629,7 +632,7 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(6
           continue;
         }
       }
-      if (unflushed >= kDenseFlush) {  // keeps the 32-bit counters of the block far from their ends
+      if (unflushed >= flush) {  // keeps the 32-bit counters of the block far from their ends
         for (int q = lane; q < kDenseCopies * kGStride; q += kWave) {
           const int32_t n = atomicExch(&hist[q], 0);
           if (n) atomicAdd(&hist_out[int64_t(g) * kHistSlots + q % kGStride], (unsigned long long)int64_t(n));
@@ -955,7 +958,8 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
     phase_begin(ctx, kPhFix);
     k_light_dense<<<unsigned(nblocks), kDenseThreads, 0, st>>>(
         c0, c1, g->ng, queues, noff, flat, g->geoff, g->gvoff, tab, W, g->edge_ptr, g->edge_nodes, g->heavy_bit,
-        g->lg_ptr, g->lg_col, g->up_first, g->recm, g->rsz, ctx->d_code_to_id3, (unsigned long long*)d_hist, tally);
+        g->lg_ptr, g->lg_col, g->up_first, g->recm, g->rsz, ctx->d_code_to_id3, (unsigned long long*)d_hist, tally,
+        (ctx->test_faults & 16) ? kDenseFlushTest : kDenseFlush);
     phase_end(ctx, kPhFix);
     k_fix_tally<<<kTallyBlocks, 256, 0, st>>>(nblocks, tally, stats);
     k_count_pairs<<<unsigned(std::min<int64_t>(blocks(ncand, 256), 256)), 256, 0, st>>>(ncand, flat, stats);

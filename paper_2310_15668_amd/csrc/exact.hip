@@ -55,8 +55,8 @@ namespace {
 constexpr int kCopies = 16;
 constexpr int kMainThreads = 512, kMainWaves = kMainThreads / kWave;
 // visits after which a wave empties the counters: they hold at most as many of
-// each wave, 4 lanes' adds a visit
-constexpr int64_t kFlushVisits = int64_t(1) << 26;
+// each wave, 4 lanes' adds a visit (few for tests of the emptying)
+constexpr int64_t kFlushVisits = int64_t(1) << 26, kFlushVisitsTest = 100;
 static_assert(kFlushVisits * kMainWaves * (kWave / kCopies) < (int64_t(1) << 32), "32-bit counters");
 
 // ---------------------------------------------------------------------------
@@ -266,7 +266,7 @@ __device__ __forceinline__ void flush_main(uint32_t (*hist)[kCopies], int first,
 __global__ __launch_bounds__(kMainThreads) void k_exact_main(
     const int64_t* __restrict__ edge_ptr, const int64_t* __restrict__ lg_ptr,
     const int32_t* __restrict__ up_first, const uint4* __restrict__ rec, WorkItems I,
-    const uint16_t* __restrict__ code_to_id3, unsigned long long* hist_out) {
+    const uint16_t* __restrict__ code_to_id3, unsigned long long* hist_out, int64_t flush_visits) {
   __shared__ uint16_t lut[kNumCodes];
   __shared__ uint32_t hist[kHistSlots][kCopies];
   // by reversed code: byte offsets of the ids' counters
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kMainThreads) void k_exact_main(
     int32_t i;
     int b;
     while (next_item(items, lane, i, b)) {
-      if (visits > kFlushVisits) {
+      if (visits > flush_visits) {
         flush_main(hist, lane, kWave, g, hist_out);
         visits = 0;
       }
@@ -1008,7 +1008,8 @@ mochy_status exact_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, int6
     if (!grouped) {
       k_exact_main<<<at_most(std::max(1u, lane_grid * 256u / unsigned(kMainThreads)), entries / kWave + g->E, kMainWaves),
                      kMainThreads, 0, st>>>(
-          g->edge_ptr, g->lg_ptr, g->up_first, g->rec, S.items(kItemsLane, a, b), ctx->d_code_to_id3, h);
+          g->edge_ptr, g->lg_ptr, g->up_first, g->rec, S.items(kItemsLane, a, b), ctx->d_code_to_id3, h,
+          (ctx->test_faults & 16) ? kFlushVisitsTest : kFlushVisits);
       continue;
     }
     if (mfma) {
