@@ -333,6 +333,19 @@ mochy_status mochy_phase_ms(const mochy_ctx* ctx, double* ms);
 #define MOCHY_NUM_EXACT_STATS 12
 mochy_status mochy_exact_stats(const mochy_ctx* ctx, int64_t* out);
 
+/* Which kernels the most recent exact counting call, mochy_profile, hyperedge
+ * sample or hyperedge profile on this context took, a bit each, for tests of the
+ * rules that choose between them (0 for a call that had nothing to do). */
+#define MOCHY_ROUTE_GROUPS 1u       /* pairs of neighbour groups */
+#define MOCHY_ROUTE_EVERY_PAIR 2u   /* pairs of neighbours */
+#define MOCHY_ROUTE_MATRIX 4u       /* matrix-core kernels launched for rows of many groups */
+#define MOCHY_ROUTE_TABLE 8u        /* light pairs by a table of overlaps */
+#define MOCHY_ROUTE_OWNERS 16u      /* light pairs owner by owner */
+#define MOCHY_ROUTE_LISTED 32u      /* light pairs listed at once (otherwise in two passes) */
+#define MOCHY_ROUTE_EDGE_GROUPS 64u /* hyperedge samples and profiles by neighbour groups */
+#define MOCHY_ROUTE_EDGE_SCAN 128u  /* hyperedge samples and profiles by scanning rows */
+uint32_t mochy_last_routes(const mochy_ctx* ctx);
+
 /* Measurement helper (not part of the method): the integer vector-ALU rate
  * the device sustains.  One timed launch of 32 waves per compute unit, every
  * lane running `iters` rounds of 32 integer vector instructions in the

@@ -43,7 +43,7 @@ EXPORTED = ("mochy_ctx_create", "mochy_ctx_destroy", "mochy_last_error", "mochy_
             "mochy_count_sampled", "mochy_profile", "mochy_motif_pattern", "mochy_parent_motif",
             "mochy_graph_stats", "mochy_phase_ms", "mochy_memo_stats", "mochy_ctx_set_option",
             "mochy_count_sampled_edges", "mochy_hyperedge_profiles", "mochy_exact_stats",
-            "mochy_calibrate_valu", "mochy_count_exact_range_noalloc")
+            "mochy_calibrate_valu", "mochy_count_exact_range_noalloc", "mochy_last_routes")
 NOALLOC_SCRATCH = 64 << 20
 NUM_EXACT_STATS = 12
 EXACT_STATS = ("rows_grouped", "groups", "groups_above", "group_pairs_full", "group_pairs_open",
@@ -119,6 +119,8 @@ def lib():
     L.mochy_memo_stats.restype = ctypes.c_int
     L.mochy_exact_stats.argtypes = [vp, vp]
     L.mochy_exact_stats.restype = ctypes.c_int
+    L.mochy_last_routes.argtypes = [vp]
+    L.mochy_last_routes.restype = u32
     L.mochy_calibrate_valu.argtypes = [vp, i64, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i64)]
     L.mochy_calibrate_valu.restype = ctypes.c_int
     L.mochy_count_sampled_edges.argtypes = [vp, vp, i64, u64, i64, vp, vp, vp, vp]
@@ -334,6 +336,15 @@ def mochy_exact_stats(ctx: Context) -> dict:
     out = np.zeros(NUM_EXACT_STATS, dtype=np.int64)
     ctx.check(lib().mochy_exact_stats(ctx.handle, _ptr(out)), "mochy_exact_stats")
     return {k: int(v) for k, v in zip(EXACT_STATS, out)}
+
+
+ROUTES = ("groups", "every_pair", "matrix", "table", "owners", "listed", "edge_groups", "edge_scan")
+
+
+def mochy_last_routes(ctx: Context) -> set:
+    """Names (``ROUTES``) of the kernels that the last counting call took, for tests."""
+    bits = lib().mochy_last_routes(ctx.handle)
+    return {name for k, name in enumerate(ROUTES) if bits >> k & 1}
 
 
 def mochy_calibrate_valu(ctx: Context, iters: int) -> tuple:

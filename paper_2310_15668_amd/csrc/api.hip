@@ -234,6 +234,7 @@ void phases_collect(mochy_ctx* c) {
 }
 
 static void phases_reset(mochy_ctx* c) {
+  c->routes = 0;
   c->phases_run = 0;
   c->phases_begun = 0;
   for (double& m : c->phase_ms) m = 0.0;
@@ -251,6 +252,8 @@ extern "C" mochy_status mochy_exact_stats(const mochy_ctx* ctx, int64_t* out) {
   std::memcpy(out, ctx->exact_stats, sizeof(ctx->exact_stats));
   return MOCHY_OK;
 }
+
+extern "C" uint32_t mochy_last_routes(const mochy_ctx* ctx) { return ctx ? ctx->routes : 0u; }
 
 extern "C" mochy_status mochy_memo_stats(const mochy_ctx* ctx, int64_t* out) {
   if (!ctx || !out) return MOCHY_EINVAL;

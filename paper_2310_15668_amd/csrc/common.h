@@ -77,6 +77,7 @@ struct mochy_ctx {
   // memos, keys memoized, most arena bytes one chunk used, list entries the
   // memo builds walked
   int64_t memo_stats[5] = {};
+  uint32_t routes = 0;                // MOCHY_ROUTE_ bits of the last call (mochy_last_routes)
   // last exact counting call (mochy_exact_stats), summed over its passes
   int64_t exact_stats[MOCHY_NUM_EXACT_STATS] = {};
 };

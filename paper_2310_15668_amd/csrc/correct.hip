@@ -943,6 +943,7 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
     }
     if (W) ctx->table_bytes = int64_t(wbytes);
   }
+  ctx->routes |= (W ? MOCHY_ROUTE_TABLE : 0u) | (flat ? MOCHY_ROUTE_LISTED : 0u);
   if (W) {
     auto dense_done = [&](mochy_status s) {
       device_free(ctx, W);
@@ -978,6 +979,7 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
   MOCHY_HIP_OR(hipStreamSynchronize(st), done);
   const int64_t nowners = ctx->h_small[504];
   if (nowners == 0) return done(MOCHY_OK);
+  ctx->routes |= MOCHY_ROUTE_OWNERS;
   launch_exclusive_scan_i64(ocount, poff, nowners + 1, tmp, st);  // ocount[nowners] is 0
   MOCHY_HIP_OR(hipMemcpyAsync(ctx->h_small + 505, poff + nowners, 8, hipMemcpyDeviceToHost, st), done);
   MOCHY_HIP_OR(hipStreamSynchronize(st), done);

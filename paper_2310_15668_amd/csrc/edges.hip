@@ -1004,6 +1004,7 @@ mochy_status edges_device(mochy_ctx* ctx, const mochy_graph* g, int64_t n0, int6
     ctx->err.clear();
     batch /= 2;
   }
+  ctx->routes |= batch ? MOCHY_ROUTE_EDGE_GROUPS : MOCHY_ROUTE_EDGE_SCAN;
   if (batch == 0) return scan_edges_device(ctx, g, n0, s, seed, kProfile, out);
   char* at = blob;
   auto take = [&](auto*& p, size_t bytes) {

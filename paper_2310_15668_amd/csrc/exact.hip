@@ -986,6 +986,7 @@ mochy_status exact_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, int6
   };
   // rows of many groups go to the matrix-core kernels
   const bool mfma = grouped && narrow && g->max_deg >= kMfmaMinDegree;
+  ctx->routes |= (grouped ? MOCHY_ROUTE_GROUPS : MOCHY_ROUTE_EVERY_PAIR) | (mfma ? MOCHY_ROUTE_MATRIX : 0u);
   const int32_t* const gna = G.gna ? (const int32_t*)(G.nsrows + 2) : nullptr;
   const RowGroups RG = {g->edge_ptr, G.goff, G.gbase, G.cap0, G.rec, (const uint32_t*)G.cnt, gna, G.elig};
   rc = build_schedule(ctx, g, c0, c1, RowKinds{g->lg_ptr, G.goff, gna, g->edge_ptr, grouped, mfma}, S);
