@@ -377,9 +377,22 @@ __global__ __launch_bounds__(256) void k_proj_degree(int64_t E, const int64_t* _
 // caches.
 constexpr int kRowThreads = 256, kRowQueue = 512;
 constexpr int kRowUnroll = 4;
+// Rows of up to kSweepRow neighbours are staged in one sweep over the bitmap, a
+// run of words to each thread, instead of tile by tile.  Those of up to
+// kShortRow, where the hypergraph has many hyperedges, are a kernel of their own
+// (kShort) that compares every neighbour's nodes and so needs no second bitmap:
+// a block of the other takes 48 KB of bitmaps for 190,000 hyperedges, to hold
+// a row of a few entries.  Flat hypergraphs, rows and records in ms, and where
+// every row went tile by tile: 190,000 hyperedges (rows of 30) 1.39, 9.95;
+// 100,000 (of 80) 0.47, 2.48; 20,000 (of 64) 0.075, 0.13.  With the line at 64
+// neighbours 1.39, 1.29 and 0.11, at 1,024 1.61, 0.47 and 0.076; 17,600 hub-heavy
+// ones 0.45 (0.43, 0.49; 0.41 tile by tile), 85,357 9.1 (9.2, 8.9; 9.4).
+constexpr int kSweepRow = 4096, kShortRow = 256;
+constexpr int64_t kShortFrom = 8192;  // hyperedges of the largest graph (above: more than one tile)
 
+template <bool kShort>
 __global__ __launch_bounds__(kRowThreads) void k_proj_rows(
-    int64_t E, const int64_t* __restrict__ ptr, const int32_t* __restrict__ nodes,
+    int64_t E, int skip, const int64_t* __restrict__ ptr, const int32_t* __restrict__ nodes,
     const int64_t* __restrict__ node_ptr, const int32_t* __restrict__ node_edges,
     const int8_t* __restrict__ heavy_bit, const EdgeInfo* __restrict__ info,
     const unsigned long long* __restrict__ hrows, const int32_t* __restrict__ row_graph,
@@ -387,22 +400,25 @@ __global__ __launch_bounds__(kRowThreads) void k_proj_rows(
     uint4* rec, uint32_t* recm, uint16_t* rsz, int32_t* flags) {
   extern __shared__ uint32_t bm[];
   __shared__ RowNodes rn;
-  __shared__ uint16_t stage[kRowThreads * 32];  // bits of the tile that are set
-  __shared__ uint2 queue[kRowQueue];            // neighbour, position: put off
+  // bits of the tile that are set, or a short enough row's entries
+  __shared__ uint32_t stage[kShort ? kShortRow : kSweepRow];
+  __shared__ uint2 queue[kShort ? 1 : kRowQueue];  // neighbour, position: put off
   __shared__ uint32_t filt[32];  // membership filter of e_i's nodes by their low 10 bits
   __shared__ uint32_t s_wave[kRowThreads / kWave], s_put;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int64_t i = blockIdx.x;
+  const int64_t base = lg_ptr[i];
+  const int d = int(lg_ptr[i + 1] - base);
+  if (kShort ? d > kShortRow : d <= skip) return;  // the other launch's (whole block)
   const int gi = row_graph[i];
   const int64_t e0 = geoff[gi], e1 = geoff[gi + 1], il = i - e0;
   const int nwords = int((e1 - e0 + 31) / 32);
   uint32_t* light = bm + nwords;
   if (tid < 32) filt[tid] = 0u;
   if (tid == 0) s_put = 0u;
-  build_row_bitmap<true>(i, e0, e1, E, ptr, nodes, node_ptr, node_edges, heavy_bit, hrows, rn, bm, light, nwords);
+  build_row_bitmap<!kShort>(i, e0, e1, E, ptr, nodes, node_ptr, node_edges, heavy_bit, hrows, rn, bm, light, nwords);
   const int a = rn.a, nh = rn.nh;
   if (tid < a) atomicOr(&filt[(rn.ei[tid] >> 5) & 31], 1u << (rn.ei[tid] & 31));
-  const int64_t base = lg_ptr[i];
   const unsigned long long hi = info[i].heavy;
   bool dup = false;
   auto write = [&](int64_t pos, const EdgeInfo& ix, uint32_t m) {
@@ -436,32 +452,32 @@ __global__ __launch_bounds__(kRowThreads) void k_proj_rows(
     }
     write(pos, ix, m);
   };
-  uint32_t found = 0;  // entries before the tile
-  for (int t0 = 0; t0 < nwords; t0 += kRowThreads) {
-    const int w = t0 + tid;
-    uint32_t bits = w < nwords ? bm[w] : 0u;
-    uint32_t incl = uint32_t(__popc(bits));
+  // staged entries before the thread's own `n`; the block's total
+  auto before = [&](uint32_t n, uint32_t& total) {
+    uint32_t incl = n;
     for (int off = 1; off < kWave; off <<= 1) {
       const uint32_t o = uint32_t(__shfl_up(int(incl), off));
       if (lane >= off) incl += o;
     }
     if (lane == kWave - 1) s_wave[wave] = incl;
     __syncthreads();
-    uint32_t at = incl - uint32_t(__popc(bits)), total = 0;
+    uint32_t at = incl - n;
+    total = 0;
     for (int y = 0; y < kRowThreads / kWave; ++y) {
       if (y < wave) at += s_wave[y];
       total += s_wave[y];
     }
-    if (w == int(il >> 5)) up_first[i] = int32_t(found + at + uint32_t(__popc(bits & ((1u << (il & 31)) - 1u))));
-    for (; bits; bits &= bits - 1u) stage[at++] = uint16_t(tid * 32 + __ffs(bits) - 1);
-    __syncthreads();
+    return at;
+  };
+  // the entries staged as bits from x0 on, written from `found` on
+  auto emit = [&](const auto* staged, int64_t x0, uint32_t found, uint32_t total) {
     for (uint32_t r0 = tid; r0 < total; r0 += kRowThreads * kRowUnroll) {
       int64_t x[kRowUnroll];
       EdgeInfo ix[kRowUnroll];
 #pragma unroll
       for (int u = 0; u < kRowUnroll; ++u) {
         const uint32_t r = min(r0 + u * kRowThreads, total - 1u);
-        x[u] = int64_t(t0) * 32 + stage[r];
+        x[u] = x0 + staged[r];
         ix[u] = info[e0 + x[u]];
       }
 #pragma unroll
@@ -481,11 +497,52 @@ __global__ __launch_bounds__(kRowThreads) void k_proj_rows(
         write(pos, ix[u], m);
       }
     }
+  };
+  auto settle = [&](uint32_t put) {
+    for (uint32_t y = tid; y < put; y += kRowThreads) compare(queue[y].x, base + queue[y].y);
+  };
+  if (kShort || d <= kSweepRow) {
+    const int per = (nwords + kRowThreads - 1) / kRowThreads | 1;  // odd: runs start in different banks
+    const int w0 = min(nwords, tid * per), w1 = min(nwords, w0 + per);
+    uint32_t n = 0, total;
+    for (int w = w0; w < w1; ++w) n += uint32_t(__popc(bm[w]));
+    uint32_t at = before(n, total);
+    for (int w = w0; w < w1; ++w) {
+      uint32_t bits = bm[w];
+      if (w == int(il >> 5)) up_first[i] = int32_t(at + uint32_t(__popc(bits & ((1u << (il & 31)) - 1u))));
+      for (; bits; bits &= bits - 1u) stage[at++] = uint32_t(w * 32 + __ffs(bits) - 1);
+    }
+    __syncthreads();
+    if (kShort) {
+      for (uint32_t r = tid; r < total; r += kRowThreads) {
+        const int64_t x = e0 + stage[r];
+        lg_col[base + r] = int32_t(x);
+        compare(x, base + r);
+      }
+    } else {
+      emit(stage, 0, 0u, total);
+      __syncthreads();
+      settle(min(s_put, uint32_t(kRowQueue)));
+    }
+    if (dup) atomicOr(flags, kFlagDup);
+    return;
+  }
+  uint16_t* const tile = reinterpret_cast<uint16_t*>(stage);  // kRowThreads words' bits
+  static_assert(kRowThreads * 32 * sizeof(uint16_t) <= kSweepRow * sizeof(uint32_t), "the tile's stage");
+  uint32_t found = 0;  // entries before the tile
+  for (int t0 = 0; t0 < nwords; t0 += kRowThreads) {
+    const int w = t0 + tid;
+    uint32_t bits = w < nwords ? bm[w] : 0u, total;
+    uint32_t at = before(uint32_t(__popc(bits)), total);
+    if (w == int(il >> 5)) up_first[i] = int32_t(found + at + uint32_t(__popc(bits & ((1u << (il & 31)) - 1u))));
+    for (; bits; bits &= bits - 1u) tile[at++] = uint16_t(tid * 32 + __ffs(bits) - 1);
+    __syncthreads();
+    emit(tile, int64_t(t0) * 32, found, total);
     found += total;
     __syncthreads();
     const uint32_t put = min(s_put, uint32_t(kRowQueue));
     if (put >= uint32_t(kRowThreads) || (put && t0 + kRowThreads >= nwords)) {
-      for (uint32_t y = tid; y < put; y += kRowThreads) compare(queue[y].x, base + queue[y].y);
+      settle(put);
       __syncthreads();
       if (tid == 0) s_put = 0u;
       __syncthreads();
@@ -655,11 +712,19 @@ mochy_status project_device(mochy_ctx* ctx, mochy_graph* g) {
   if ((rc = device_alloc(ctx, (void**)&g->rsz, size_t(std::max<int64_t>(twoW, 1)) * 2)) != MOCHY_OK) { cleanup(); return rc; }
   g->bytes += size_t(twoW) * 26;
   phase_begin(ctx, kPhRows);
-  if ((rc = allow_lds(ctx, (const void*)k_proj_rows, 2 * bm_bytes)) != MOCHY_OK) return fail(rc);
-  if (E > 0)
-    k_proj_rows<<<unsigned(E), kRowThreads, 2 * bm_bytes, st>>>(
-        E, g->edge_ptr, g->edge_nodes, g->node_ptr, g->node_edges, g->heavy_bit, info, hrows, g->row_graph, g->geoff,
+  const bool split = g->max_graph_edges > kShortFrom;
+  if (split) {
+    if ((rc = allow_lds(ctx, (const void*)k_proj_rows<true>, bm_bytes)) != MOCHY_OK) return fail(rc);
+    k_proj_rows<true><<<unsigned(E), kRowThreads, bm_bytes, st>>>(
+        E, 0, g->edge_ptr, g->edge_nodes, g->node_ptr, g->node_edges, g->heavy_bit, info, hrows, g->row_graph, g->geoff,
         g->lg_ptr, g->lg_col, g->up_first, g->rec, g->recm, g->rsz, ctx->d_flags);
+  }
+  if (E > 0 && (!split || g->max_deg > kShortRow)) {
+    if ((rc = allow_lds(ctx, (const void*)k_proj_rows<false>, 2 * bm_bytes)) != MOCHY_OK) return fail(rc);
+    k_proj_rows<false><<<unsigned(E), kRowThreads, 2 * bm_bytes, st>>>(
+        E, split ? kShortRow : -1, g->edge_ptr, g->edge_nodes, g->node_ptr, g->node_edges, g->heavy_bit, info, hrows,
+        g->row_graph, g->geoff, g->lg_ptr, g->lg_col, g->up_first, g->rec, g->recm, g->rsz, ctx->d_flags);
+  }
   phase_end(ctx, kPhRows);
   phase_begin(ctx, kPhRecords);
   // upper-row prefix (hyperwedge order for sampling)
