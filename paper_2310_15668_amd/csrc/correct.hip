@@ -518,6 +518,7 @@ __global__ __launch_bounds__(kOffsetThreads) void k_overlap_offsets(int ng, cons
     sum += (geoff[g + 1] - geoff[g]) * overlap_of(geoff[g], geoff[g + 1], c0, c1).stride;
   part[tid] = sum;
   __syncthreads();
+  if (g0 >= g1) return;
   int64_t at = 0;  // of the threads before
   for (int x = 0; x < tid; ++x) at += part[x];
   for (int g = g0; g < g1; ++g) {
