@@ -487,6 +487,14 @@ constexpr int kOverlapChunk = 32768;  // bytes of a row formed in LDS at a time
 //   3,000 of 100 (78)                     5.9   0.78
 //   100 of 1,000 (6,110)                  0.66  0.85
 //   1,000 of 1,000 (6,100)                6.2   7.8
+// A range of up to half the centres always has its table where the rows are short
+// ones (below kLongStride): owner by owner every pair is still to be listed and
+// every owner's row to be built, whatever the range (table, owner by owner):
+//   100,000 of 200,000 nodes, a 10th      (1 GB)    0.57  0.76
+//   the same, a quarter                   (2.5 GB)  0.79  0.79
+//   100,000 of 5,000 nodes, a quarter     (2.5 GB)  10.6  14.2
+//   190,000 of 100,000 nodes, a 10th      (3.6 GB)  2.1   6.0
+//   the same, a quarter: long rows        (9 GB)    8.4   6.0
 constexpr size_t kSmallTable = size_t(512) << 20, kSmallTables = size_t(8) << 30;
 constexpr int kFewGraphs = 16;
 constexpr int64_t kGraphSlots = 4096;
@@ -924,7 +932,8 @@ mochy_status correct_device(mochy_ctx* ctx, const mochy_graph* g, int64_t c0, in
     }
     bool pays = wbytes > 0 && wbytes <= size_t(ctx->total_mem / 6) && !(ctx->test_faults & 1) &&
                 (g->ng <= kFewGraphs || ncand >= g->ng * kGraphSlots);
-    if (pays && (most > kSmallTable || wbytes > kSmallTables)) {
+    const bool narrow = c1 - c0 < kLongStride && 2 * (c1 - c0) <= E;
+    if (pays && !narrow && (most > kSmallTable || wbytes > kSmallTables)) {
       MOCHY_HIP_OR(hipMemcpyAsync(ctx->h_small + 504, work, 16, hipMemcpyDeviceToHost, st), done);
       MOCHY_HIP_OR(hipStreamSynchronize(st), done);
       // a range's columns of the rows are as many of their entries

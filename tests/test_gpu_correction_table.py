@@ -44,8 +44,11 @@ def test_flat(E, V, size):
     with M.Context(0) as ctx:
         torch.cuda.synchronize()
         before = torch.cuda.mem_get_info(0)[0]
-        st, *_ = _check(M, ctx, h, (None, (h.num_edges // 2, h.num_edges // 2 + 300)))
+        st, *_ = _check(M, ctx, h)
         held = before - torch.cuda.mem_get_info(0)[0]
+        # ranges: of 300, of half the centres and of more
+        half = h.num_edges // 2
+        _check(M, ctx, h, ((half, half + 300), (0, half), (half - 3, h.num_edges), (11, 11 + min(32767, half))))
         assert st["light_pairs"] > 1000 and st["fix_changed"] > 0
         if table > 512 << 20:
             assert held < table // 2, (held, table)

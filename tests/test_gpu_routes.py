@@ -51,6 +51,20 @@ def test_exact(name, faults, groups, want):
         g.close()
 
 
+@pytest.mark.parametrize("centres,want", [(5000, {G, T, L}), (32767, {G, T, L}), (32768, {G, O, L}), (40000, {G, O, L})])
+def test_ranges(centres, want):
+    """Ranges of up to half the centres, in rows of up to 32,768 bytes, have the
+    table although all centres have not."""
+    import paper_2310_15668_amd as M
+    h = _flat(70000, 9000, 2)
+    assert 2 * 32768 <= h.num_edges < 80000
+    with M.Context(0) as ctx:
+        g = M.mochy_project(ctx, h.edge_ptr, h.edge_nodes, h.num_nodes)
+        M.mochy_count_exact_range(ctx, g, 7, 7 + centres)
+        assert M.mochy_last_routes(ctx) == want
+        g.close()
+
+
 @pytest.mark.parametrize("n,want", [(16, {G, T, L}), (17, {G, O, L})])
 def test_batch(n, want):
     import paper_2310_15668_amd as M
