@@ -87,13 +87,13 @@ def summary_values(summary, source):
 NUM_CUS, CLOCK_HZ, LANES = 256, 2.4e9, 64
 VALU_PEAK_DERIVED = NUM_CUS * LANES * CLOCK_HZ
 
-# What the pair kernels cannot do without, in CU cycles per 64 pairs (a wave):
+# What the pair kernels cannot do without, in CU cycles per 64 pairs (a wave),
+# each measured alone (profiles/pair_rates.md):
 #  * a pair of neighbour groups that both have a member above the centre: one
-#    LDS add of j's counts to a counter of k's, 4.1 cycles with every lane at a
-#    word of its own;
-#  * any other pair (counted only when open): two half-rate vector instructions
-#    for two rows, 1.1 cycles, beside 0.75 of MFMA.
-FULL_PAIR_CYCLES, OPEN_PAIR_CYCLES = 4.1, 1.85
+#    LDS add of j's counts to a counter of k's, every lane at a word of its own;
+#  * any other pair (counted only when open): its share of three FP4 products
+#    and of a packed subtract and a dot product for two rows.
+FULL_PAIR_CYCLES, OPEN_PAIR_CYCLES = 4.05, 1.92
 # Algorithmic bytes of the light-pair kernel: the overlap table's byte of every
 # scanned entry, and for every centre it finds a 4-byte record mask and a
 # 2-byte size word.
@@ -763,7 +763,7 @@ def medium_exact(args):
                      "frac": achieved / peak, "traffic": measured_traffic(),
                      "model": f"{FULL_PAIR_CYCLES} CU cycles per 64 pairs of neighbour groups counted in full (an LDS "
                               f"add), {OPEN_PAIR_CYCLES} per 64 others (vector and matrix issue)",
-                     "peak_source": "cycle costs measured alone, 256 CUs at 2.4 GHz",
+                     "peak_source": "cycle costs measured alone (profiles/pair_rates.md), 256 CUs at 2.4 GHz",
                      "kernel_ms": pair_ms, "group_pairs_full": xs["group_pairs_full"],
                      "group_pairs_open": xs["group_pairs_open"],
                      "candidates_per_s": st["candidates"] / (pair_ms * 1e-3),

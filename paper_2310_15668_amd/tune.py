@@ -5,7 +5,9 @@ their counts:
 
 * ``MOCHY_OPT_BATCH_LAUNCH``: one launch over the whole batch (1, the
   default), which overlaps the graphs' tails, or one launch per graph (2);
-* ``MOCHY_OPT_PAIR_BLOCKS``: blocks launched per compute unit.
+* ``MOCHY_OPT_PAIR_BLOCKS``: blocks launched per compute unit, of the kernel
+  that takes a pair per lane.  The matrix-core kernels of long rows hold a
+  compute unit's LDS with a fixed number of blocks and are not changed by it.
 
 Which is faster depends on how the batch's work is spread over its graphs.
 ``tune_batch`` counts a representative batch once per candidate, checks that
