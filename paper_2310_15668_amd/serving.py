@@ -45,7 +45,10 @@ def _correction_bytes(E: int, ptr, nodes, deg) -> tuple:
     lists = 8 * (len(deg) + 1) + 80 * E + 5 * pairs
     if 8 * slots > CANDIDATE_LIST:
         return lists, 0, 0
-    longest = min(E - 1, int(np.add.reduceat(deg[np.asarray(nodes)] - 1, np.asarray(ptr)[:-1]).max()))
+    # arrays that the library refuses come here as well: offsets may be out of order
+    before = np.concatenate(([0], np.cumsum(deg[np.asarray(nodes)] - 1)))
+    at = np.clip(np.asarray(ptr), 0, len(nodes))
+    longest = min(E - 1, max(0, int((before[at[1:]] - before[at[:-1]]).max())))
     return lists + 4 * len(nodes) + 8 * slots, E * ((E + 15) // 16 * 16), pairs * longest
 
 

@@ -67,3 +67,15 @@ def test_without_light_nodes():
     h = from_edge_lists([sorted(e) for e in edges] + [[0, 64]], 65)
     assert request_bytes([csr(h)]) == base(h)
     assert request_bytes([]) == 0 and request_bytes([(np.zeros(1, np.int64), np.zeros(0, np.int32), 0)]) == 16 + 9
+
+
+@pytest.mark.parametrize("ptr", [
+    np.append(np.arange(0, 401, 2), 400),        # the last hyperedge is empty
+    np.insert(np.arange(0, 401, 2), 5, 8),       # one in the middle
+    np.append(np.arange(0, 401, 2), 500),        # past the end
+    np.insert(np.arange(0, 401, 2), 3, -1)])     # not increasing
+def test_what_the_library_refuses(ptr):
+    # such a request is admitted, and its error is given to whoever waits for it
+    nodes = np.arange(200).repeat(2)
+    deg = np.bincount(nodes)
+    assert request_bytes([(ptr, nodes, 200)]) >= 100 * int((deg * (deg - 1) // 2).sum())
